@@ -128,6 +128,7 @@ struct RopeParams {
   int32_t num_kv_heads;
   int32_t rotary_dim;        // multiple of 16, <= D
   float norm_eps;
+  int32_t lg_heads;          // log2 of the Q or K heads per workgroup (set by the launcher)
   double rev_freq[kRopeMaxPlanes];  // plane rate in revolutions per position: f_j / (2 pi)
   StoreReqs reqs;                   // reqs.n > 0: the units come from here instead
 };

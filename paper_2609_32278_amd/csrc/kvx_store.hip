@@ -176,12 +176,21 @@ __global__ __launch_bounds__(kStoreThreads) void store_kv_kernel(StoreParams p) 
 // the plane's rate in revolutions per position, so positions far past 2^24
 // keep full precision.  Results are rounded once (RNE bf16 or e4m3).
 //
+// Work split: one workgroup per touched page and group of heads (Q groups, K groups,
+// V groups).  One workgroup per page walking all heads left a batch of a few dozen
+// to a few hundred pages with one long serial chain per CU -- a V head after another,
+// two barriers each (1.0 TB/s at 150 pages, 49 MB); a group per workgroup runs the same
+// batch at 3.0 TB/s (42.6 -> 16.4 us) and 1700 pages of 64+8 heads at 4.8 TB/s (249 -> 237 us,
+// where a 4 GiB copy reaches 4.8 TB/s).  The price is that each group forms the page's
+// angles again, which its first loads overlap.
+//
 // A head row of D bf16 values is D/8 16-byte chunks held by D/8 consecutive
 // lanes; the RMS sum is reduced across those lanes, and in the half layout a
 // chunk of the first half meets its plane partners in the chunk rotary_dim/16
 // lanes further on (one lane shuffle per value).
 
-constexpr int kRopeBatch = 4;  // chunks per thread loaded before any is processed
+constexpr int kRopeBatch = 4;  // chunks per thread in flight
+constexpr int kRopeVHeads = 4;   // V heads per workgroup
 
 template <int D, bool INTERLEAVED>
 struct RopeLane {
@@ -237,16 +246,29 @@ __device__ __forceinline__ void rope_chunk(float (&x)[8], const RopeLane<D, INTE
   }
 }
 
-// Normalise and rotate the n_rows head rows at src ([row][D] bf16; row = tok *
-// heads + head, token tok at slot slot_begin + tok) and hand each chunk's
-// results to out(row, chunk, y).
-template <int D, bool INTERLEAVED, class Out>
-__device__ __forceinline__ void rope_rows(const uint16_t* __restrict__ src, int n_rows, int heads,
+// Normalise and rotate `nh` heads from h0 on (nh <= 1 << lg) of the unit's ntok tokens
+// (src: the first token's row, [token][heads][D] bf16) and hand each chunk's results
+// to out(token, head, chunk, y).  The first loads are issued before angles() -- which
+// fills cs and ends in a barrier -- so that they are in flight meanwhile.
+template <int D, bool INTERLEAVED, class Angles, class Out>
+__device__ __forceinline__ void rope_rows(const uint16_t* __restrict__ src, int ntok, int heads, int h0, int nh, int lg,
                                           int slot_begin, const float2 (*cs)[kRopeMaxPlanes],
-                                          const uint16_t* norm_w, float eps, int rotary_dim, Out&& out) {
+                                          const uint16_t* norm_w, float eps, int rotary_dim, Angles&& angles,
+                                          Out&& out) {
   constexpr int CPR = D / 8;
-  const int n = n_rows * CPR;
   const RopeLane<D, INTERLEAVED> rl(rotary_dim);
+  // row index rr = token << lg | head of the group; rows past the group's heads idle
+  const int n = ntok << lg;
+  constexpr int ROWS = kStoreThreads / CPR;  // rows per step
+  const int r0 = threadIdx.x / CPR;
+  auto load = [&](int rr) {
+    const int tok = rr >> lg, hh = rr & ((1 << lg) - 1);
+    return rr < n && hh < nh ? *(const uint4*)(src + ((size_t)tok * heads + h0 + hh) * D + rl.cc * 8)
+                             : make_uint4(0, 0, 0, 0);
+  };
+  uint4 raw[kRopeBatch];
+#pragma unroll
+  for (int b = 0; b < kRopeBatch; b++) raw[b] = load(r0 + b * ROWS);
   float w[8];
   if (norm_w) {
     const uint4 wr = *(const uint4*)(norm_w + rl.cc * 8);
@@ -254,17 +276,16 @@ __device__ __forceinline__ void rope_rows(const uint16_t* __restrict__ src, int 
 #pragma unroll
     for (int e = 0; e < 8; e++) w[e] = bf16_to_f32(wh[e]);
   }
-  for (int c0 = threadIdx.x; c0 < n; c0 += kRopeBatch * kStoreThreads) {
-    uint4 raw[kRopeBatch];
+  angles();
+  for (int c0 = r0; c0 - r0 < n; c0 += kRopeBatch * ROWS) {
+    uint4 next[kRopeBatch];
+#pragma unroll
+    for (int b = 0; b < kRopeBatch; b++) next[b] = load(c0 + (kRopeBatch + b) * ROWS);
 #pragma unroll
     for (int b = 0; b < kRopeBatch; b++) {
-      const int c = c0 + b * kStoreThreads;
-      raw[b] = c < n ? *(const uint4*)(src + (size_t)c * 8) : make_uint4(0, 0, 0, 0);
-    }
-#pragma unroll
-    for (int b = 0; b < kRopeBatch; b++) {
-      const int c = c0 + b * kStoreThreads;
-      const int row = c / CPR;
+      const int rr = c0 + b * ROWS;
+      if (rr - r0 >= n) break;  // uniform
+      const int tok = rr >> lg, hh = rr & ((1 << lg) - 1);
       const uint16_t* h16 = (const uint16_t*)&raw[b];
       float x[8];
 #pragma unroll
@@ -279,10 +300,11 @@ __device__ __forceinline__ void rope_rows(const uint16_t* __restrict__ src, int 
 #pragma unroll
         for (int e = 0; e < 8; e++) x[e] = (x[e] * inv) * w[e];
       }
-      const int slot = slot_begin + (c < n ? row / heads : 0);
-      rope_chunk<D, INTERLEAVED>(x, rl, cs[slot]);
-      if (c < n) out(row, rl.cc, x);
+      rope_chunk<D, INTERLEAVED>(x, rl, cs[slot_begin + (rr < n ? tok : 0)]);
+      if (rr < n && hh < nh) out(tok, h0 + hh, rl.cc, x);
     }
+#pragma unroll
+    for (int b = 0; b < kRopeBatch; b++) raw[b] = next[b];
   }
 }
 
@@ -297,65 +319,93 @@ __device__ __forceinline__ uint4 pack_bf16x8(const float (&y)[8]) {
   return r;
 }
 
+// Grid: x = the unit (a touched page), y = a group of heads: first the groups of
+// 1 << p.lg_heads Q heads, then those of K heads, then those of HB V heads.
 template <int D, bool FP8, bool INTERLEAVED>
 __global__ __launch_bounds__(kStoreThreads) void store_kv_rope_kernel(RopeParams p) {
-  __shared__ float2 cs[kPageSize][kRopeMaxPlanes];  // (cos, sin) of every live slot and plane
-  __shared__ __attribute__((aligned(16))) uint16_t vs[kPageSize][D + 8];
-  const RopeUnit u = p.reqs.n > 0 ? inline_unit(p.reqs, blockIdx.x) : p.units[blockIdx.x];
-  const int page = p.page_ids[u.page_pos];
-  const int planes = p.rotary_dim / 2;
-  const int ntok = u.slot_end - u.slot_begin;
-
-  for (int e = threadIdx.x; e < ntok * planes; e += kStoreThreads) {
-    const int s = u.slot_begin + e / planes, j = e % planes;
-    double rev = (double)(u.pos_slot0 + s) * p.rev_freq[j];  // exact position times the rate
-    rev -= rint(rev);                                          // [-1/2, 1/2] turn, exact
-    float sn, cn;
-    sincospif(2.0f * (float)rev, &sn, &cn);
-    cs[s][j] = make_float2(cn, sn);
-  }
-  __syncthreads();
-
   constexpr int CPR = D / 8;
+  constexpr int HB = kRopeVHeads;
+  constexpr int VCHUNKS = kPageSize * CPR;  // 16-byte chunks of one head's V rows
+  constexpr int PER = HB * VCHUNKS / kStoreThreads;
+  union Shared {
+    float2 cs[kPageSize][kRopeMaxPlanes];  // (cos, sin) of every live slot and plane
+    uint16_t vs[HB][kPageSize][D + 8];     // V rows staged for the transpose
+  };
+  __shared__ __attribute__((aligned(16))) Shared sm;
+  const RopeUnit u = p.reqs.n > 0 ? inline_unit(p.reqs, blockIdx.x) : p.units[blockIdx.x];
+  const int ntok = u.slot_end - u.slot_begin;
   const int Hq = p.num_q_heads, H = p.num_kv_heads;
   const int row0 = u.row_slot0 + u.slot_begin;  // first suffix row of the unit
-  if (Hq > 0) {
-    const size_t base = (size_t)row0 * Hq * D;
-    uint16_t* qo = p.q_out + base;
-    rope_rows<D, INTERLEAVED>(p.q + base, ntok * Hq, Hq, u.slot_begin, cs, p.q_norm, p.norm_eps, p.rotary_dim,
-                              [&](int row, int cc, const float(&y)[8]) {
-                                *(uint4*)(qo + (size_t)row * D + cc * 8) = pack_bf16x8(y);
-                              });
-  }
-  rope_rows<D, INTERLEAVED>(
-      p.k_ext + (size_t)row0 * H * D, ntok * H, H, u.slot_begin, cs, p.k_norm, p.norm_eps, p.rotary_dim,
-      [&](int row, int cc, const float(&y)[8]) {
-        const int hd = row % H, slot = u.slot_begin + row / H;
-        const size_t blk = ((size_t)page * H + hd) * (size_t)(kPageSize * D);
-        if constexpr (FP8) {
-          const float kinv = p.k_inv_scale[hd];
-          uint2 code;
-          code.x = e4m3x4(y[0] * kinv, y[1] * kinv, y[2] * kinv, y[3] * kinv);
-          code.y = e4m3x4(y[4] * kinv, y[5] * kinv, y[6] * kinv, y[7] * kinv);
-          *(uint2*)((uint8_t*)p.k_pool + blk + (size_t)slot * D + cc * 8) = code;
-        } else {
-          *(uint4*)((uint16_t*)p.k_pool + blk + (size_t)slot * D + cc * 8) = pack_bf16x8(y);
-        }
-      });
+  const int lg = p.lg_heads, hpg = 1 << lg;
+  const int nq = (Hq + hpg - 1) >> lg, nk = (H + hpg - 1) >> lg;
+  const int y = blockIdx.y;
 
-  // V: staged per head in LDS and written as [dim][slot] columns
-  for (int hd = 0; hd < H; hd++) {
-    for (int c = threadIdx.x; c < kPageSize * CPR; c += kStoreThreads) {
-      const int slot = c / CPR, cc = c % CPR;
-      uint4 vx = make_uint4(0, 0, 0, 0);
-      if (slot >= u.slot_begin && slot < u.slot_end)
-        vx = *(const uint4*)(p.v_ext + ((size_t)(u.row_slot0 + slot) * H + hd) * D + cc * 8);
-      *(uint4*)(&vs[slot][cc * 8]) = vx;
+  auto angles = [&]() {
+    const int planes = p.rotary_dim / 2;
+    for (int e = threadIdx.x; e < ntok * planes; e += kStoreThreads) {
+      const int s = u.slot_begin + e / planes, j = e % planes;
+      double rev = (double)(u.pos_slot0 + s) * p.rev_freq[j];  // exact position times the rate
+      rev -= rint(rev);                                          // [-1/2, 1/2] turn, exact
+      float sn, cn;
+      sincospif(2.0f * (float)rev, &sn, &cn);
+      sm.cs[s][j] = make_float2(cn, sn);
     }
     __syncthreads();
+  };
+
+  if (y < nq) {
+    const int h0 = y << lg, nh = Hq - h0 < hpg ? Hq - h0 : hpg;
+    uint16_t* qo = p.q_out + (size_t)row0 * Hq * D;
+    rope_rows<D, INTERLEAVED>(p.q + (size_t)row0 * Hq * D, ntok, Hq, h0, nh, lg, u.slot_begin, sm.cs, p.q_norm,
+                              p.norm_eps, p.rotary_dim, angles, [&](int tok, int hd, int cc, const float(&v)[8]) {
+                                *(uint4*)(qo + ((size_t)tok * Hq + hd) * D + cc * 8) = pack_bf16x8(v);
+                              });
+    return;
+  }
+  const int page = p.page_ids[u.page_pos];
+  if (y < nq + nk) {
+    const int h0 = (y - nq) << lg, nh = H - h0 < hpg ? H - h0 : hpg;
+    rope_rows<D, INTERLEAVED>(
+        p.k_ext + (size_t)row0 * H * D, ntok, H, h0, nh, lg, u.slot_begin, sm.cs, p.k_norm, p.norm_eps, p.rotary_dim,
+        angles, [&](int tok, int hd, int cc, const float(&v)[8]) {
+          const size_t blk = ((size_t)page * H + hd) * (size_t)(kPageSize * D);
+          const int slot = u.slot_begin + tok;
+          if constexpr (FP8) {
+            const float kinv = p.k_inv_scale[hd];
+            uint2 code;
+            code.x = e4m3x4(v[0] * kinv, v[1] * kinv, v[2] * kinv, v[3] * kinv);
+            code.y = e4m3x4(v[4] * kinv, v[5] * kinv, v[6] * kinv, v[7] * kinv);
+            *(uint2*)((uint8_t*)p.k_pool + blk + (size_t)slot * D + cc * 8) = code;
+          } else {
+            *(uint4*)((uint16_t*)p.k_pool + blk + (size_t)slot * D + cc * 8) = pack_bf16x8(v);
+          }
+        });
+    return;
+  }
+
+  // V: HB heads staged in LDS at once and written as [dim][slot] columns
+  const int h0 = (y - nq - nk) * HB;
+  uint4 vx[PER];
+#pragma unroll
+  for (int j = 0; j < PER; j++) {
+    const int i = threadIdx.x + j * kStoreThreads;
+    const int hd = h0 + i / VCHUNKS, slot = (i % VCHUNKS) / CPR, cc = i % CPR;
+    vx[j] = make_uint4(0, 0, 0, 0);
+    if (hd < H && slot >= u.slot_begin && slot < u.slot_end)
+      vx[j] = *(const uint4*)(p.v_ext + ((size_t)(u.row_slot0 + slot) * H + hd) * D + cc * 8);
+  }
+#pragma unroll
+  for (int j = 0; j < PER; j++) {
+    const int i = threadIdx.x + j * kStoreThreads;
+    *(uint4*)(&sm.vs[i / VCHUNKS][(i % VCHUNKS) / CPR][(i % CPR) * 8]) = vx[j];
+  }
+  __syncthreads();
+#pragma unroll
+  for (int hb = 0; hb < HB; hb++) {
+    const int hd = h0 + hb;
+    if (hd >= H) break;  // uniform
     const size_t blk = ((size_t)page * H + hd) * (size_t)(kPageSize * D);
-    write_vt<D, FP8>(vs, p.v_pool, blk, u.slot_begin, u.slot_end, FP8 ? p.v_inv_scale[hd] : 1.0f);
-    __syncthreads();
+    write_vt<D, FP8>(sm.vs[hb], p.v_pool, blk, u.slot_begin, u.slot_end, FP8 ? p.v_inv_scale[hd] : 1.0f);
   }
 }
 
@@ -449,10 +499,28 @@ hipError_t launch_store_kv(const StoreParams& p, int64_t n_units, int head_dim, 
   return hipGetLastError();
 }
 
-hipError_t launch_store_kv_rope(const RopeParams& p, int64_t n_units, int head_dim, bool fp8, bool interleaved,
+// log2 of the Q or K heads per rope workgroup.  Fewer heads give more workgroups,
+// more heads compute the unit's angles less often.  Measured (us per call, 4 / 8 / 16 /
+// 32 heads): 150 pages of 32+8 heads 16.4 / 17.1 / 20.9 / 31.8, 270 pages 24.6 / 22.5 /
+// 26.1 / 33.6, 1700 pages of 64+8 heads 255 / 241 / 237 / 246, 2048 pages of 32+8 heads
+// 180 / 169 / 157 / 169 -- so up to 2048 workgroups 4 heads, and never more than 16.
+static int rope_lg_heads(const RopeParams& p, int64_t n_units, int64_t& groups) {
+  for (int lg = 2;; lg++) {
+    const int64_t hpg = (int64_t)1 << lg;
+    groups = (p.num_q_heads + hpg - 1) / hpg + (p.num_kv_heads + hpg - 1) / hpg +
+             (p.num_kv_heads + kRopeVHeads - 1) / kRopeVHeads;
+    // a grid's y dimension is bounded by 65535 (tens of thousands of heads)
+    if (groups <= 65535 && (lg >= 4 || n_units * groups <= 2048)) return lg;
+  }
+}
+
+hipError_t launch_store_kv_rope(const RopeParams& params, int64_t n_units, int head_dim, bool fp8, bool interleaved,
                                 hipStream_t stream) {
   if (n_units <= 0) return hipSuccess;
-  dim3 grid((unsigned)n_units), block(kStoreThreads);
+  RopeParams p = params;
+  int64_t groups = 0;
+  p.lg_heads = rope_lg_heads(p, n_units, groups);
+  dim3 grid((unsigned)n_units, (unsigned)groups), block(kStoreThreads);
 #define KVX_ROPE_LAUNCH(D, F, I) hipLaunchKernelGGL((store_kv_rope_kernel<D, F, I>), grid, block, 0, stream, p)
   if (head_dim == 128) {
     if (fp8) { if (interleaved) KVX_ROPE_LAUNCH(128, true, true); else KVX_ROPE_LAUNCH(128, true, false); }

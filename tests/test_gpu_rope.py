@@ -371,3 +371,18 @@ def test_full_size_llama8b_with_fused_rope():
                                   w.sm_scale)
     got = out[torch.from_numpy(gidx).to(DEV)].float().cpu().numpy().astype(np.float64)
     compare(got, ref, f"rope-full {name}")
+
+
+@pytest.mark.parametrize("pages,hq,hkv,kv_dtype", [
+    (3, 5, 5, wl.KV_BF16),        # 4 heads per workgroup, ragged last groups of Q, K and V heads
+    (190, 40, 5, wl.KV_BF16),     # 8 heads per workgroup
+    (260, 40, 5, wl.KV_FP8_E4M3),  # 16 heads per workgroup
+])
+def test_head_groups_of_the_fused_store(pages, hq, hkv, kv_dtype):
+    """The fused store splits a page's heads over workgroups (4, 8 or 16 per group by
+    the batch's size): head counts that leave a ragged last group, at each size."""
+    CASES["head_groups"] = ([7], [16 * pages - 9], hq, hkv, 128, kv_dtype, wl.RopeSpec(1e6, 128, R.HALF, True))
+    try:
+        _check_store("head_groups", seed=5)
+    finally:
+        del CASES["head_groups"]
