@@ -478,7 +478,10 @@ __device__ __forceinline__ void k_offsets(int (&koff)[Geom<D>::KSTEPS], int n, i
 __device__ __forceinline__ int v_offset(int n, int h) { return n * 32 + ((h ^ ((n >> 3) & 1)) * 16); }
 
 // Epilogue: lane (n, h) holds dims 32*b + 8*(i/4) + 4*h + i%4 of its row; O = o * vscale / l
-// rounded to bf16 with the LSE, or the fp32 partial result of a split part.
+// rounded to bf16 with the LSE, or the fp32 partial result of a split part.  Partial
+// results keep the accumulator layout, [32-row block][b][i / 4][lane] of four floats: a
+// wave's store is 1 KiB in one piece (in row order it was 64 pieces of 16 bytes: 256 parts
+// of 1024 keys took 54.6 us with those, 51.3 us with these, whole kernel).
 template <int D>
 __device__ __forceinline__ void write_result(const AttnParams& p, const Rows& r, const f32x16 (&o)[Geom<D>::DB],
                                              float l_run, float m_run, float vscale) {
@@ -501,8 +504,8 @@ __device__ __forceinline__ void write_result(const AttnParams& p, const Rows& r,
       }
       if (p.lse != nullptr && r.h == 0) p.lse[(size_t)(r.u.qo_row0 + r.tok) * p.num_q_heads + r.hq] = lse_val;
     }
-  } else {
-    float* dst = p.o_part + ((size_t)r.u.part * kTileRows + r.rho) * D;
+  } else if (r.valid) {  // the merge reads no other rows
+    float* dst = p.o_part + (size_t)r.u.part * kTileRows * D + (r.rho >> 5) * (32 * D) + r.lane * 4;
 #pragma unroll
     for (int b = 0; b < G::DB; b++) {
 #pragma unroll
@@ -512,7 +515,7 @@ __device__ __forceinline__ void write_result(const AttnParams& p, const Rows& r,
         w[1] = o[b][4 * g4 + 1] * inv;
         w[2] = o[b][4 * g4 + 2] * inv;
         w[3] = o[b][4 * g4 + 3] * inv;
-        *(f32x4*)(dst + 32 * b + 8 * g4 + 4 * r.h) = w;
+        *(f32x4*)(dst + (4 * b + g4) * 256) = w;
       }
     }
     if (r.h == 0) p.lse_part[(size_t)r.u.part * kTileRows + r.rho] = lse_val;
@@ -1122,42 +1125,57 @@ __global__ __launch_bounds__(kAttnThreads, 1) void extend_attn_fp8_kernel(AttnPa
 }
 
 // Combine the parts of split tiles: o = sum_p e^{lse_p - M} o_p / sum_p e^{lse_p - M}.
-// Rows of a tile per merge workgroup (256 lanes, one 16-byte column group each).
-template <int D>
-constexpr int kMergeRows = 256 / (D / 4);
-static_assert(kTileRows % kMergeRows<128> == 0 && kTileRows % kMergeRows<64> == 0, "whole row blocks");
-
+// Workgroup (merge, 32-row block, 32 dims b): wave g4 combines dims 32 b + 8 g4 .. +8 of
+// the block, lane by lane in the layout write_result stores, with the loads of UNROLL
+// parts in flight.  256 parts of 256 rows (33.5 MB): 7.6 us, against 17.9 us for a serial
+// loop over parts in row order.
 template <int D>
 __global__ __launch_bounds__(256) void merge_kernel(MergeParams p) {
-  // workgroup (merge, row block): kMergeRows rows of the tile, one 16-byte column
-  // group of one row per lane, so that a merge of few tiles still spreads over the CUs
+  constexpr int UNROLL = 8;
+  constexpr int DB = Geom<D>::DB;
   const MergeUnit mu = p.merges[blockIdx.x];
   const int kv_head = mu.head_ntok >> 16;
   const int ntok = mu.head_ntok & 0xFFFF;
-  constexpr int C4 = D / 4;
-  const int rho = (int)blockIdx.y * kMergeRows<D> + (int)threadIdx.x / C4;
-  const int c = ((int)threadIdx.x % C4) * 4;
+  const int blk = (int)blockIdx.y / DB, b = (int)blockIdx.y % DB;
+  const int lane = threadIdx.x & 63, g4 = threadIdx.x >> 6;
+  const int rho = blk * 32 + (lane & 31);
   const int tok = rho / p.group;
   if (tok >= ntok) return;
-  const int hq = kv_head * p.group + (rho - tok * p.group);
-  float mx = -INFINITY;
-  for (int q = 0; q < mu.nparts; q++) mx = fmaxf(mx, p.lse_part[(size_t)(mu.part0 + q) * kTileRows + rho]);
-  float wsum = 0.0f;
+  const float* lse = p.lse_part + (size_t)mu.part0 * kTileRows + rho;
+  const float* op = p.o_part + (size_t)mu.part0 * kTileRows * D + blk * (32 * D) + (4 * b + g4) * 256 + lane * 4;
+  float mx = -INFINITY, wsum = 0.0f;
   f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-  for (int q = 0; q < mu.nparts; q++) {
-    const float l = p.lse_part[(size_t)(mu.part0 + q) * kTileRows + rho];
-    const float w = (l == -INFINITY) ? 0.0f : __expf(l - mx);
-    const f32x4 v = *(const f32x4*)(p.o_part + ((size_t)(mu.part0 + q) * kTileRows + rho) * D + c);
-    acc += v * w;
-    wsum += w;
+  for (int q0 = 0; q0 < mu.nparts; q0 += UNROLL) {
+    float l[UNROLL];
+    f32x4 x[UNROLL];
+    float m_new = mx;
+#pragma unroll
+    for (int j = 0; j < UNROLL; j++) {
+      const bool in = q0 + j < mu.nparts;
+      l[j] = in ? lse[(size_t)(q0 + j) * kTileRows] : -INFINITY;
+      x[j] = in ? *(const f32x4*)(op + (size_t)(q0 + j) * kTileRows * D) : f32x4{0.f, 0.f, 0.f, 0.f};
+    }
+#pragma unroll
+    for (int j = 0; j < UNROLL; j++) m_new = fmaxf(m_new, l[j]);
+    const float alpha = mx == -INFINITY ? 0.0f : __expf(mx - m_new);
+    wsum *= alpha;
+    acc *= alpha;
+#pragma unroll
+    for (int j = 0; j < UNROLL; j++) {
+      const float w = (l[j] == -INFINITY) ? 0.0f : __expf(l[j] - m_new);
+      acc += x[j] * w;
+      wsum += w;
+    }
+    mx = m_new;
   }
   const float inv = wsum > 0.0f ? 1.0f / wsum : 0.0f;
+  const int hq = kv_head * p.group + (rho - tok * p.group);
   const size_t row = (size_t)(mu.qo_row0 + tok) * p.num_q_heads + hq;
   uint2 w2;
   w2.x = pack_bf16(acc[0] * inv, acc[1] * inv);
   w2.y = pack_bf16(acc[2] * inv, acc[3] * inv);
-  *(uint2*)(p.out + row * D + c) = w2;
-  if (p.lse != nullptr && c == 0) p.lse[row] = mx + __logf(wsum);
+  *(uint2*)(p.out + row * D + 32 * b + 8 * g4 + 4 * (lane >> 5)) = w2;
+  if (p.lse != nullptr && b == 0 && g4 == 0 && lane < 32) p.lse[row] = mx + __logf(wsum);
 }
 
 }  // namespace
@@ -1182,9 +1200,9 @@ hipError_t launch_merge(const MergeParams& p, int64_t n_merges, int head_dim, hi
   if (n_merges <= 0) return hipSuccess;
   const dim3 block(256);
   if (head_dim == 128)
-    hipLaunchKernelGGL((merge_kernel<128>), dim3((unsigned)n_merges, kTileRows / kMergeRows<128>), block, 0, stream, p);
+    hipLaunchKernelGGL((merge_kernel<128>), dim3((unsigned)n_merges, kTileRows / 32 * Geom<128>::DB), block, 0, stream, p);
   else
-    hipLaunchKernelGGL((merge_kernel<64>), dim3((unsigned)n_merges, kTileRows / kMergeRows<64>), block, 0, stream, p);
+    hipLaunchKernelGGL((merge_kernel<64>), dim3((unsigned)n_merges, kTileRows / 32 * Geom<64>::DB), block, 0, stream, p);
   return hipGetLastError();
 }
 

@@ -53,7 +53,7 @@ struct AttnParams {
   const void* v_pool;
   const int32_t* page_ids;
   const AttnUnit* units;
-  float* o_part;          // fp32 [parts, kTileRows, D]
+  float* o_part;          // fp32 [parts, kTileRows * D], in the accumulators' order (write_result)
   float* lse_part;        // fp32 [parts, kTileRows]
   const float* k_scale;   // fp8 pool: device [Hkv]
   const float* v_scale;
