@@ -10,10 +10,11 @@
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
-#include <map>
+#include <functional>
 #include <numeric>
+#include <queue>
 #include <string>
-#include <tuple>
+#include <utility>
 #include <vector>
 
 #include "kvx_internal.h"
@@ -261,195 +262,295 @@ struct Plan {
   int64_t n_parts = 0;
 };
 
+// A tile of suffix tokens of one request; every KV head has the same tiles.
+struct Tile {
+  int32_t r, tok0, ntok;
+  int64_t kend, qpos0;  // keys [0, kend); position of the first token
+};
+
+// What a unit costs besides its iterations over 64 keys, in such iterations (about 1.7 us
+// at head_dim 128 on a busy chip, 0.9 us at 64): its first loads and its epilogue; the
+// fp32 result of a part of 256 rows, written and read again; the merge launch.  Set so
+// that the split chosen below is the fastest one, or within 5% of it, on 14 batches timed
+// with ten forced split lengths each (units alone take 11.5 and 8.0 us for one tile).
+struct UnitCosts {
+  double start, part, merge;
+};
+constexpr UnitCosts kUnitCosts128{8.0, 4.0, 3.0}, kUnitCosts64{11.0, 4.0, 3.0};
+
+// Duration, in iterations, of the longest-first schedule of one KV head's units on its
+// share of the 256 workgroup slots, when the key ranges are split every `split` keys (0 = not at
+// all).  Equal units are scheduled as groups.
+double schedule_length(const std::vector<Tile>& tiles, int64_t split, int32_t Hkv, int32_t tile_tok,
+                       const UnitCosts& k, int64_t& parts) {
+  const int BN = kvx::kTileKeys;
+  std::vector<std::pair<double, int64_t>> units;  // (cost, how many)
+  auto add = [&](double c, int64_t n) {
+    if (!units.empty() && units.back().first == c) units.back().second += n;
+    else units.push_back({c, n});
+  };
+  parts = 0;
+  for (const Tile& t : tiles) {
+    const int64_t nb = split > 0 ? t.qpos0 / split : 0;  // boundaries split, 2 split, ... <= qpos0
+    const double extra = nb > 0 ? k.start + k.part * t.ntok / tile_tok : k.start;
+    if (nb > 0) {
+      add((double)(split / BN) + extra, nb);
+      parts += nb + 1;
+    }
+    add((double)ceil_div(t.kend - nb * split, BN) + extra, 1);
+  }
+  std::sort(units.begin(), units.end(), [](const auto& x, const auto& y) { return x.first > y.first; });
+  // slots as groups of equal load, least loaded first
+  typedef std::pair<double, int64_t> Slots;
+  std::priority_queue<Slots, std::vector<Slots>, std::greater<Slots>> free;
+  free.push({0.0, std::max<int64_t>(1, kPlanSlots / Hkv)});
+  double end = 0.0;
+  for (auto [cost, n] : units) {
+    while (n > 0) {
+      Slots s = free.top();
+      free.pop();
+      const int64_t m = std::min(n, s.second);
+      if (s.second > m) free.push({s.first, s.second - m});
+      free.push({s.first + cost, m});
+      end = std::max(end, s.first + cost);
+      n -= m;
+    }
+  }
+  return parts > 0 ? end + k.merge : end;
+}
+
+// Length (keys, a multiple of 64) of the parts key ranges are split into, 0 = no split.
+//   * A batch whose longest tile is at most an eighth of a slot's share of the work runs
+//     unsplit, and so does one whose unsplit schedule is within 4% of perfect balance.
+//   * Otherwise the schedule is worked out for no split, for the shortest parts that give
+//     one and two units per slot, and for lengths in steps of 1.3 from 1.5 times a slot's
+//     share to a fifth of it; the shortest schedule wins, the last ones only by 3% (a
+//     200000-token prefix under 300 tokens: 1713 us in two whole rounds, 1694 us in five).
+//     One of a single round of parts counts 6% of a part more: it ends with its slowest CU
+//     (the XCDs' clocks differ by 4-7%) and has no shorter unit to even that out.  Parts
+//     have at least 4 iterations.
+int64_t choose_split(const std::vector<Tile>& tiles, int32_t Hkv, int32_t tile_tok, int32_t D, int64_t max_parts) {
+  const int BN = kvx::kTileKeys;
+  const UnitCosts& k = D == 128 ? kUnitCosts128 : kUnitCosts64;
+  int64_t total = 0, longest = 0;
+  for (const Tile& t : tiles) {
+    const int64_t c = ceil_div(t.kend, BN);
+    total += c;
+    longest = std::max(longest, c);
+  }
+  const double slots = std::max(1.0, (double)kPlanSlots / Hkv);  // per KV head
+  const double share = (double)total / slots;                    // iterations per slot
+  if ((double)longest * 8 <= share) return 0;
+  int64_t best_split = 0, parts = 0;
+  double best = schedule_length(tiles, 0, Hkv, tile_tok, k, parts);
+  if (best <= 1.04 * (share + k.start * std::max(1.0, (double)tiles.size() / slots))) return 0;
+  auto units_at = [&](int64_t len) {  // iterations per part; the count never grows with it
+    int64_t n = 0;
+    for (const Tile& t : tiles) n += t.qpos0 / (len * BN) + 1;
+    return n;
+  };
+  auto try_length = [&](int64_t len, double margin) {
+    const double least = std::max((double)len, share + k.start * (double)units_at(len) / slots);
+    if ((least + k.merge) * margin >= best) return;  // cannot win
+    double t = schedule_length(tiles, len * BN, Hkv, tile_tok, k, parts);
+    if (parts == 0 || parts * Hkv > max_parts) return;
+    if ((double)parts <= slots) t += 0.06 * (double)len;
+    t *= margin;
+    if (t < best) {
+      best = t;
+      best_split = len * BN;
+    }
+  };
+  for (const int rounds : {1, 2}) {
+    int64_t lo = 4, hi = longest;
+    while (lo < hi) {
+      const int64_t mid = lo + (hi - lo) / 2;
+      if ((double)units_at(mid) <= rounds * slots) hi = mid;
+      else lo = mid + 1;
+    }
+    try_length(lo, 1.0);
+  }
+  double len = std::min((double)longest / 2, 1.5 * share);
+  for (int i = 0; i < 10 && len >= std::max(4.0, share / 5); i++, len /= 1.3) try_length((int64_t)len, 1.03);
+  return best_split;
+}
+
 // Work plan of extend_attention.
 //   * every request's suffix is cut into tiles of tile_tok tokens (x group query heads
 //     = 256 rows) per KV head; a tile covers keys [0, P + last token of the tile];
-//   * when the batch has too little work to fill the chip, or a tile's key range is
-//     far longer than the average work per workgroup slot, the key range is split at
-//     multiples of the tile width into parts merged by log-sum-exp afterwards (the
-//     parts lengthened slightly when that saves a nearly empty last round of units);
+//   * key ranges may be split at multiples of the tile width into parts, merged by
+//     log-sum-exp afterwards (choose_split);
 //   * each (request, KV head) is bound to one XCD (KV head h -> XCD h % 8 when the
 //     head count is a multiple of 8), so the workgroups that stream the same K/V
 //     pages share one L2; for other head counts each (request, KV head, part of a
 //     split key range) is bound greedily by cost, so that a batch of few long
 //     requests still spreads its parts over all eight XCDs (the parts of one key
 //     range, read by every tile of the request, stay together);
-//   * within an XCD, requests go longest first and a request's tiles longest first.
-int make_plan(const kvx_batch* b, const std::vector<int64_t>& qo, int32_t Hq, int32_t Hkv, int32_t split_keys,
-              int64_t max_parts, Plan& plan) {
+//   * within an XCD, the units of a split batch, or of one of less than four rounds, go
+//     longest first, those over one key range next to each other.  Other batches keep
+//     each request together instead, requests by their longest tile and tiles longest
+//     first, which is nearly longest first and streams one request's pages at a time.  (By
+//     total work of the request, a request of few long tiles came last: 16 agents with
+//     4k-32k prefixes, 3.19 -> 2.85 ms.)
+int make_plan(const kvx_batch* b, const std::vector<int64_t>& qo, int32_t Hq, int32_t Hkv, int32_t D,
+              int32_t split_keys, int64_t max_parts, Plan& plan) {
   const int G = Hq / Hkv;
   const int tile_tok = kvx::kTileRows / G;
   const int BN = kvx::kTileKeys;
 
-  struct Tile { int r, h, tok0, ntok; int64_t kend, qpos0, cost; };
-  std::vector<Tile> tiles;
-  int64_t total_cost = 0, max_cost = 0;
-  for (int r = 0; r < b->num_reqs; r++) {
+  // requests by their longest tile
+  std::vector<int32_t> order;
+  for (int r = 0; r < b->num_reqs; r++)
+    if (b->extend_lens[r] > 0) order.push_back(r);
+  std::stable_sort(order.begin(), order.end(), [&](int32_t x, int32_t y) {
+    return (int64_t)b->prefix_lens[x] + b->extend_lens[x] > (int64_t)b->prefix_lens[y] + b->extend_lens[y];
+  });
+  std::vector<Tile> tiles;  // request by request, a request's longest tile first
+  for (const int32_t r : order) {
     const int64_t P = b->prefix_lens[r], E = b->extend_lens[r];
-    for (int64_t t0 = 0; t0 < E; t0 += tile_tok) {
-      const int ntok = (int)std::min<int64_t>(tile_tok, E - t0);
-      const int64_t kend = P + t0 + ntok;
-      const int64_t cost = ceil_div(kend, BN);
-      for (int h = 0; h < Hkv; h++) {
-        tiles.push_back(Tile{r, h, (int)t0, ntok, kend, P + t0, cost});
-        total_cost += cost;
-        max_cost = std::max(max_cost, cost);
-      }
+    for (int64_t t0 = (E - 1) / tile_tok * tile_tok; t0 >= 0; t0 -= tile_tok) {
+      const int64_t ntok = std::min<int64_t>(tile_tok, E - t0);
+      tiles.push_back(Tile{r, (int32_t)t0, (int32_t)ntok, P + t0 + ntok, P + t0});
     }
   }
 
-  // split length in keys (a multiple of BN), 0 = no split
-  int64_t split = 0;
-  if (split_keys > 0) {
-    split = split_keys;
-  } else if (!tiles.empty()) {
-    const int64_t avg = total_cost / kPlanSlots;            // tiles of keys per slot
-    const int64_t allowed = std::max<int64_t>(avg / 2, 16);  // at least 1024 keys per part
-    if (max_cost > allowed) split = allowed * BN;
-  }
-  if (split > 0) {
-    // keep the number of parts bounded
-    for (;;) {
-      int64_t parts = 0;
-      for (const Tile& t : tiles) {
-        const int64_t nb = t.qpos0 / split;  // boundaries split, 2 split, ... <= qpos0
-        if (nb > 0) parts += nb + 1;
-      }
-      if (parts <= max_parts) break;
-      split *= 2;
-    }
-    if (split_keys <= 0) {
-      // Whole rounds: a unit count a little past a multiple of the 256 slots leaves a
-      // nearly empty last round.  Lengthen the parts (in whole tiles) when that
-      // removes it for less than half a round (the units spilling into it are often
-      // a tile's short last parts): the smallest split below split * (1 + 1 / 2k)
-      // that yields at most k rounds of units (the count never grows with the
-      // split, so a bisection finds it).
-      std::vector<std::pair<int64_t, int64_t>> starts;  // (first query position, tiles)
-      for (const Tile& t : tiles) {
-        if (!starts.empty() && starts.back().first == t.qpos0) starts.back().second++;
-        else starts.push_back({t.qpos0, 1});
-      }
-      auto units_at = [&](int64_t s) {
-        int64_t n = 0;
-        for (const auto& q : starts) n += (q.first / s + 1) * q.second;
-        return n;
-      };
-      const int64_t k = (units_at(split) - 1) / kPlanSlots;
-      if (k >= 1) {
-        const int64_t target = k * kPlanSlots;
-        int64_t lo = split / BN + 1, hi = (split + split / (2 * k) - 1) / BN;  // split lengths in tiles
-        if (lo <= hi && units_at(hi * BN) <= target) {
-          while (lo < hi) {
-            const int64_t mid = lo + (hi - lo) / 2;
-            if (units_at(mid * BN) <= target) hi = mid;
-            else lo = mid + 1;
-          }
-          split = lo * BN;
-        }
-      }
-    }
+  int64_t split = split_keys > 0 ? split_keys : choose_split(tiles, Hkv, tile_tok, D, max_parts);
+  auto boundaries = [&](const Tile& t) { return split > 0 ? t.qpos0 / split : 0; };  // split, 2 split, ... <= qpos0
+  while (split > 0) {  // keep the number of parts bounded
+    int64_t parts = 0;
+    for (const Tile& t : tiles)
+      if (const int64_t nb = boundaries(t)) parts += nb + 1;
+    if (parts * Hkv <= max_parts) break;
+    split *= 2;
   }
 
-  // Key ranges of a tile: [0, split), [split, 2 split), ... up to the last boundary
-  // <= qpos0, then the rest to kend; one range when unsplit.
-  auto ranges_of = [&](const Tile& t) {
-    std::vector<std::pair<int64_t, int64_t>> rg;
-    if (split > 0 && t.qpos0 / split > 0) {
-      int64_t kb = 0;
-      for (int64_t bnd = split; bnd <= t.qpos0; bnd += split) {
-        rg.push_back({kb, bnd});
-        kb = bnd;
-      }
-      rg.push_back({kb, t.kend});
-    } else {
-      rg.push_back({0, t.kend});
-    }
-    return rg;
-  };
-  // XCD of (request, head, part index).  Multiples of 8 heads: head h -> XCD h % 8
-  // for every part.  Otherwise greedy by cost over (request, head, part) keys,
-  // costliest first, each to the least loaded XCD.
+  // XCD of a unit.  Multiples of 8 heads: head h -> XCD h % 8.  Otherwise greedy by cost,
+  // costliest first, each to the least loaded XCD: the tiles over one (request, head,
+  // part), in runs of at most a sixth of an XCD's share of the work (13 requests of 2
+  // heads, a request and head together: the busiest XCD 1.45 times the mean).
   const bool by_head = Hkv % kvx::kNumXcd == 0;
-  std::map<std::tuple<int, int, int64_t>, int> bind_xcd;
+  std::vector<int32_t> run_of(tiles.size(), 0);  // the tile's run within its request
   if (!by_head) {
-    std::map<std::tuple<int, int, int64_t>, int64_t> bind_cost;
-    for (const Tile& t : tiles) {
-      const auto rg = ranges_of(t);
-      for (size_t i = 0; i < rg.size(); i++)
-        bind_cost[{t.r, t.h, (int64_t)i}] += ceil_div(rg[i].second - rg[i].first, BN);
+    int64_t total = 0, in_run = 0;
+    for (const Tile& t : tiles) total += ceil_div(t.kend, BN);
+    // an unsplit batch of less than four rounds: every tile by itself, since a tile
+    // more or less is a third of a round there
+    const int64_t most =
+        split == 0 && (int64_t)tiles.size() * Hkv < 4 * kPlanSlots ? 0 : total * Hkv / (6 * kvx::kNumXcd);
+    for (size_t k = 0; k < tiles.size(); k++) {
+      const int64_t c = ceil_div(boundaries(tiles[k]) > 0 ? split : tiles[k].kend, BN);
+      const bool same = k > 0 && tiles[k].r == tiles[k - 1].r;
+      const bool fits = same && in_run + c <= most;
+      run_of[k] = !same ? 0 : run_of[k - 1] + (fits ? 0 : 1);
+      in_run = fits ? in_run + c : c;
     }
-    std::vector<std::pair<std::tuple<int, int, int64_t>, int64_t>> order(bind_cost.begin(), bind_cost.end());
-    std::stable_sort(order.begin(), order.end(), [](const auto& a, const auto& c) { return a.second > c.second; });
+  }
+  std::vector<size_t> bind_at((size_t)b->num_reqs, 0);  // first entry of a request: [head][run][part]
+  std::vector<int32_t> bind_parts((size_t)b->num_reqs, 0), bind_n((size_t)b->num_reqs, 0);  // parts; runs x parts
+  std::vector<uint8_t> bind_xcd;
+  if (!by_head) {
+    std::vector<int64_t> cost;
+    for (size_t first = 0; first < tiles.size();) {
+      size_t last = first;
+      while (last < tiles.size() && tiles[last].r == tiles[first].r) last++;
+      const size_t r = (size_t)tiles[first].r;
+      // the request's longest tile has the most parts, its last tile is in the last run
+      bind_at[r] = cost.size();
+      bind_parts[r] = (int32_t)boundaries(tiles[first]) + 1;
+      bind_n[r] = (run_of[last - 1] + 1) * bind_parts[r];
+      cost.resize(cost.size() + (size_t)bind_n[r] * Hkv, 0);
+      for (size_t k = first; k < last; k++) {
+        const int64_t nb = boundaries(tiles[k]);
+        for (int64_t i = 0; i <= nb; i++)
+          for (int32_t h = 0; h < Hkv; h++)
+            cost[bind_at[r] + (size_t)h * bind_n[r] + (size_t)(run_of[k] * bind_parts[r] + i)] +=
+                ceil_div((i < nb ? (i + 1) * split : tiles[k].kend) - i * split, BN);
+      }
+      first = last;
+    }
+    std::vector<int32_t> by_cost(cost.size());
+    std::iota(by_cost.begin(), by_cost.end(), 0);
+    std::stable_sort(by_cost.begin(), by_cost.end(),
+                     [&](int32_t x, int32_t y) { return cost[(size_t)x] > cost[(size_t)y]; });
+    bind_xcd.resize(cost.size());
     int64_t load[kvx::kNumXcd] = {0};
-    for (const auto& kc : order) {
+    for (const int32_t i : by_cost) {
       int best = 0;
       for (int x = 1; x < kvx::kNumXcd; x++)
         if (load[x] < load[best]) best = x;
-      bind_xcd[kc.first] = best;
-      load[best] += kc.second;
+      bind_xcd[(size_t)i] = (uint8_t)best;
+      load[best] += cost[(size_t)i];
     }
   }
-  // request order: total cost, longest first
-  std::vector<int64_t> req_cost((size_t)b->num_reqs, 0);
-  for (const Tile& t : tiles) req_cost[(size_t)t.r] += t.cost;
-  std::vector<int> req_rank((size_t)b->num_reqs);
-  {
-    std::vector<int> order((size_t)b->num_reqs);
-    std::iota(order.begin(), order.end(), 0);
-    std::stable_sort(order.begin(), order.end(), [&](int a, int c) { return req_cost[(size_t)a] > req_cost[(size_t)c]; });
-    for (int i = 0; i < b->num_reqs; i++) req_rank[(size_t)order[(size_t)i]] = i;
-  }
-  std::stable_sort(tiles.begin(), tiles.end(), [&](const Tile& a, const Tile& c) {
-    if (req_rank[(size_t)a.r] != req_rank[(size_t)c.r]) return req_rank[(size_t)a.r] < req_rank[(size_t)c.r];
-    if (a.cost != c.cost) return a.cost > c.cost;
-    return a.h < c.h;
-  });
 
-  std::vector<std::vector<AttnUnit>> per_xcd(kvx::kNumXcd);
-  std::vector<std::vector<kvx_work_item>> per_xcd_items(kvx::kNumXcd);
+  struct Placed {
+    AttnUnit u;
+    int32_t tok0;
+  };
+  std::vector<Placed> per_xcd[kvx::kNumXcd];
   plan.merges.clear();
   plan.n_parts = 0;
-  for (const Tile& t : tiles) {
-    AttnUnit u;
-    u.qo_row0 = (int32_t)(qo[(size_t)t.r] + t.tok0);
-    u.q_pos0 = (int32_t)t.qpos0;
-    u.page_base = b->page_indptr[t.r];
-    u.head_ntok = (t.h << 16) | t.ntok;
-    u.req = t.r;
-    const std::vector<std::pair<int64_t, int64_t>> ranges = ranges_of(t);
-    const bool is_split = ranges.size() > 1;
-    if (is_split) {
-      MergeUnit m;
-      m.qo_row0 = u.qo_row0;
-      m.head_ntok = u.head_ntok;
-      m.part0 = (int32_t)plan.n_parts;
-      m.nparts = (int32_t)ranges.size();
-      plan.merges.push_back(m);
+  for (size_t first = 0; first < tiles.size();) {  // one request at a time
+    size_t last = first;
+    while (last < tiles.size() && tiles[last].r == tiles[first].r) last++;
+    const int32_t r = tiles[first].r;
+    // part numbers: a tile's parts are consecutive for each KV head
+    std::vector<int64_t> part0;
+    for (size_t k = first; k < last; k++) {
+      const Tile& t = tiles[k];
+      const int64_t nb = boundaries(t);
+      part0.push_back(plan.n_parts);
+      if (nb == 0) continue;
+      for (int32_t h = 0; h < Hkv; h++)
+        plan.merges.push_back(MergeUnit{(int32_t)(qo[(size_t)r] + t.tok0), (h << 16) | t.ntok,
+                                        (int32_t)(plan.n_parts + h * (nb + 1)), (int32_t)nb + 1});
+      plan.n_parts += (nb + 1) * Hkv;
     }
-    for (size_t i = 0; i < ranges.size(); i++) {
-      const auto& rg = ranges[i];
-      const int x = by_head ? t.h % kvx::kNumXcd : bind_xcd.at({t.r, t.h, (int64_t)i});
-      u.key_begin = (int32_t)rg.first;
-      u.key_end = (int32_t)rg.second;
-      u.part = is_split ? (int32_t)plan.n_parts++ : -1;
-      per_xcd[(size_t)x].push_back(u);
-      per_xcd_items[(size_t)x].push_back(kvx_work_item{t.r, t.h, t.tok0, t.ntok, u.key_begin, u.key_end, u.part, x});
+    const int64_t ranges = boundaries(tiles[first]) + 1;
+    for (int64_t i = 0; i < ranges; i++) {
+      for (size_t k = first; k < last; k++) {
+        const Tile& t = tiles[k];
+        const int64_t nb = boundaries(t);
+        if (i > nb) continue;
+        AttnUnit u;
+        u.qo_row0 = (int32_t)(qo[(size_t)r] + t.tok0);
+        u.q_pos0 = (int32_t)t.qpos0;
+        u.page_base = b->page_indptr[r];
+        u.key_begin = (int32_t)(i * split);
+        u.key_end = (int32_t)(i < nb ? (i + 1) * split : t.kend);
+        u.req = r;
+        for (int32_t h = 0; h < Hkv; h++) {
+          const int x = by_head ? h % kvx::kNumXcd
+                                : bind_xcd[bind_at[(size_t)r] + (size_t)h * bind_n[(size_t)r] +
+                                           (size_t)(run_of[k] * bind_parts[(size_t)r] + i)];
+          u.head_ntok = (h << 16) | t.ntok;
+          u.part = nb > 0 ? (int32_t)(part0[k - first] + h * (nb + 1) + i) : -1;
+          per_xcd[x].push_back(Placed{u, t.tok0});
+        }
+      }
     }
+    first = last;
   }
+  if (plan.n_parts > 0 || (int64_t)tiles.size() * Hkv < 4 * kPlanSlots)
+    for (auto& v : per_xcd)
+      std::stable_sort(v.begin(), v.end(), [](const Placed& x, const Placed& y) {
+        return x.u.key_end - x.u.key_begin > y.u.key_end - y.u.key_begin;
+      });
   size_t longest = 0;
   for (const auto& v : per_xcd) longest = std::max(longest, v.size());
   plan.units.clear();
   plan.items.clear();
+  plan.units.reserve(longest * kvx::kNumXcd);
+  plan.items.reserve(longest * kvx::kNumXcd);
   for (size_t i = 0; i < longest; i++) {
     for (int x = 0; x < kvx::kNumXcd; x++) {
-      if (i < per_xcd[(size_t)x].size()) {
-        plan.units.push_back(per_xcd[(size_t)x][i]);
-        plan.items.push_back(per_xcd_items[(size_t)x][i]);
+      if (i < per_xcd[x].size()) {
+        const AttnUnit& u = per_xcd[x][i].u;
+        plan.units.push_back(u);
+        plan.items.push_back(kvx_work_item{u.req, u.head_ntok >> 16, per_xcd[x][i].tok0, u.head_ntok & 0xFFFF,
+                                           u.key_begin, u.key_end, u.part, x});
       } else {
         AttnUnit pad{};
-        pad.key_begin = 0;
-        pad.key_end = 0;
         pad.part = -1;
         plan.units.push_back(pad);
         plan.items.push_back(kvx_work_item{-1, 0, 0, 0, 0, 0, -1, x});
@@ -1093,7 +1194,7 @@ int extend_attention_plan(const kvx_batch* batch, int32_t num_q_heads, int32_t n
       out_items = std::move(dp.items);
     } else {
       Plan plan;
-      if (int rc = make_plan(batch, qo, num_q_heads, num_kv_heads, split_keys, kMaxParts, plan)) return rc;
+      if (int rc = make_plan(batch, qo, num_q_heads, num_kv_heads, head_dim, split_keys, kMaxParts, plan)) return rc;
       out_items = std::move(plan.items);
     }
   }
@@ -1134,7 +1235,7 @@ int kvx::attention_call(kvx_pool* pool, const kvx_batch* batch, const void* q, i
   const int D = pool->head_dim;
   const size_t part_bytes = (size_t)kvx::kTileRows * (D + 1) * sizeof(float);
   Plan plan;
-  if (int rc = make_plan(batch, qo, num_q_heads, pool->num_kv_heads, pool->split_keys, buf.max_parts(part_bytes),
+  if (int rc = make_plan(batch, qo, num_q_heads, pool->num_kv_heads, D, pool->split_keys, buf.max_parts(part_bytes),
                          plan))
     return rc;
   // one upload: units, then merges
