@@ -243,6 +243,8 @@ int store_kv_rope(kvx_pool *pool, const kvx_batch *batch, const kvx_rope *rope, 
  * A decode step -- every request has at most one suffix token, and at most 16
  * query heads share a KV head -- runs a dedicated decode kernel (key chunks of
  * each request and KV head streamed from HBM); the result is the same operation.
+ * In a batch that mixes one-token suffixes with longer ones, the one-token suffixes
+ * may take the same code next to the prefill tiles.
  * Uses a library-owned device workspace (grown with hipMallocAsync when a batch
  * needs more than any earlier one; at most 2 GiB of partial results).  Errors: EINVAL, EUNSUPPORTED, ERANGE (validation
  * mode), ENOMEM, EHIP.  R = 0 or T = 0: no-op.
@@ -328,8 +330,8 @@ int kv_pool_set_split_keys(kvx_pool *pool, int32_t keys);
  * ranges, and adds one more bf16 rounding of q (2^-9 relative per element): the
  * error against the exact attention grows where scores are large (about twice
  * the default's at query scale 4).  The prefill kernel of an fp8 pool always takes
- * this form (its e4m3 keys dominate the error), and decode steps are always
- * exact.  The softmax itself (Section 2's prefill over the uncached suffix) is
+ * this form (its e4m3 keys dominate the error), and decode steps (and one-token
+ * suffixes that take the decode code) are always exact.  The softmax itself (Section 2's prefill over the uncached suffix) is
  * unchanged.  A setting of the pool: takes effect for calls queued after it, from
  * the pool's one host thread.  Errors: EINVAL (pool NULL, enable not 0 or 1).
  */

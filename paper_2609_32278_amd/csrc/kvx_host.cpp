@@ -260,6 +260,15 @@ struct Plan {
   std::vector<MergeUnit> merges;
   std::vector<kvx_work_item> items;  // same order, for inspection
   int64_t n_parts = 0;
+  // decode units among the units (mixed batches)
+  bool mixed = false;
+  std::vector<kvx::DecodeMerge> dec_merges;
+  int64_t dec_parts = 0;
+};
+
+// Bounds on the partial results of a plan.
+struct PartLimits {
+  int64_t prefill, decode;
 };
 
 // A tile of suffix tokens of one request; every KV head has the same tiles.
@@ -278,11 +287,23 @@ struct UnitCosts {
 };
 constexpr UnitCosts kUnitCosts128{8.0, 4.0, 3.0}, kUnitCosts64{11.0, 4.0, 3.0};
 
+// Decode units of a mixed batch, in the same measure: 64 keys stream in about 0.4
+// iterations.
+constexpr double kDecodePerIter = 0.4;
+// Share of them spread evenly over the prefill units, which they overlap; the rest fill up
+// the end.  3 prefilling requests with 61 decoding ones: 632 us, 636 us with three quarters,
+// 668 us with all of them spread, 683 us with all at the end.
+constexpr double kDecodeSpread = 0.6;
+struct Filler {
+  int64_t units = 0;  // of one KV head
+  double cost = 0.0;  // of one unit
+};
+
 // Duration, in iterations, of the longest-first schedule of one KV head's units on its
 // share of the 256 workgroup slots, when the key ranges are split every `split` keys (0 = not at
 // all).  Equal units are scheduled as groups.
 double schedule_length(const std::vector<Tile>& tiles, int64_t split, int32_t Hkv, int32_t tile_tok,
-                       const UnitCosts& k, int64_t& parts) {
+                       const UnitCosts& k, const Filler& filler, int64_t& parts) {
   const int BN = kvx::kTileKeys;
   std::vector<std::pair<double, int64_t>> units;  // (cost, how many)
   auto add = [&](double c, int64_t n) {
@@ -299,6 +320,7 @@ double schedule_length(const std::vector<Tile>& tiles, int64_t split, int32_t Hk
     }
     add((double)ceil_div(t.kend - nb * split, BN) + extra, 1);
   }
+  if (filler.units > 0) units.push_back({filler.cost, filler.units});
   std::sort(units.begin(), units.end(), [](const auto& x, const auto& y) { return x.first > y.first; });
   // slots as groups of equal load, least loaded first
   typedef std::pair<double, int64_t> Slots;
@@ -329,7 +351,8 @@ double schedule_length(const std::vector<Tile>& tiles, int64_t split, int32_t Hk
 //     One of a single round of parts counts 6% of a part more: it ends with its slowest CU
 //     (the XCDs' clocks differ by 4-7%) and has no shorter unit to even that out.  Parts
 //     have at least 4 iterations.
-int64_t choose_split(const std::vector<Tile>& tiles, int32_t Hkv, int32_t tile_tok, int32_t D, int64_t max_parts) {
+int64_t choose_split(const std::vector<Tile>& tiles, int32_t Hkv, int32_t tile_tok, int32_t D, const Filler& filler,
+                     int64_t max_parts) {
   const int BN = kvx::kTileKeys;
   const UnitCosts& k = D == 128 ? kUnitCosts128 : kUnitCosts64;
   int64_t total = 0, longest = 0;
@@ -339,10 +362,10 @@ int64_t choose_split(const std::vector<Tile>& tiles, int32_t Hkv, int32_t tile_t
     longest = std::max(longest, c);
   }
   const double slots = std::max(1.0, (double)kPlanSlots / Hkv);  // per KV head
-  const double share = (double)total / slots;                    // iterations per slot
+  const double share = ((double)total + filler.cost * (double)filler.units) / slots;  // iterations per slot
   if ((double)longest * 8 <= share) return 0;
   int64_t best_split = 0, parts = 0;
-  double best = schedule_length(tiles, 0, Hkv, tile_tok, k, parts);
+  double best = schedule_length(tiles, 0, Hkv, tile_tok, k, filler, parts);
   if (best <= 1.04 * (share + k.start * std::max(1.0, (double)tiles.size() / slots))) return 0;
   auto units_at = [&](int64_t len) {  // iterations per part; the count never grows with it
     int64_t n = 0;
@@ -352,7 +375,7 @@ int64_t choose_split(const std::vector<Tile>& tiles, int32_t Hkv, int32_t tile_t
   auto try_length = [&](int64_t len, double margin) {
     const double least = std::max((double)len, share + k.start * (double)units_at(len) / slots);
     if ((least + k.merge) * margin >= best) return;  // cannot win
-    double t = schedule_length(tiles, len * BN, Hkv, tile_tok, k, parts);
+    double t = schedule_length(tiles, len * BN, Hkv, tile_tok, k, filler, parts);
     if (parts == 0 || parts * Hkv > max_parts) return;
     if ((double)parts <= slots) t += 0.06 * (double)len;
     t *= margin;
@@ -392,16 +415,26 @@ int64_t choose_split(const std::vector<Tile>& tiles, int32_t Hkv, int32_t tile_t
 //     first, which is nearly longest first and streams one request's pages at a time.  (By
 //     total work of the request, a request of few long tiles came last: 16 agents with
 //     4k-32k prefixes, 3.19 -> 2.85 ms.)
+//   * one-token suffixes next to longer ones become decode units, key chunks of the (request,
+//     KV head), when through tiles they would take a slot at least 8 iterations (below
+//     that the merge of their chunks costs what they save).
 int make_plan(const kvx_batch* b, const std::vector<int64_t>& qo, int32_t Hq, int32_t Hkv, int32_t D,
-              int32_t split_keys, int64_t max_parts, Plan& plan) {
+              int32_t split_keys, const PartLimits& limits, bool allow_mixed, Plan& plan) {
   const int G = Hq / Hkv;
   const int tile_tok = kvx::kTileRows / G;
   const int BN = kvx::kTileKeys;
 
+  int64_t one_token = 0, one_keys = 0;  // iterations and keys of one-token suffixes, all KV heads
+  for (int r = 0; r < b->num_reqs; r++)
+    if (b->extend_lens[r] == 1) {
+      one_token += Hkv * ceil_div((int64_t)b->prefix_lens[r] + 1, BN);
+      one_keys += Hkv * ((int64_t)b->prefix_lens[r] + 1);
+    }
+  plan.mixed = allow_mixed && G <= kvx::kDecodeMaxGroup && one_token >= 8 * kPlanSlots;
   // requests by their longest tile
   std::vector<int32_t> order;
   for (int r = 0; r < b->num_reqs; r++)
-    if (b->extend_lens[r] > 0) order.push_back(r);
+    if (b->extend_lens[r] > (plan.mixed ? 1 : 0)) order.push_back(r);
   std::stable_sort(order.begin(), order.end(), [&](int32_t x, int32_t y) {
     return (int64_t)b->prefix_lens[x] + b->extend_lens[x] > (int64_t)b->prefix_lens[y] + b->extend_lens[y];
   });
@@ -414,13 +447,58 @@ int make_plan(const kvx_batch* b, const std::vector<int64_t>& qo, int32_t Hq, in
     }
   }
 
-  int64_t split = split_keys > 0 ? split_keys : choose_split(tiles, Hkv, tile_tok, D, max_parts);
+  // decode units: chunks of 2048 keys (long enough to hide their start, short enough to
+  // fill gaps), shorter where that leaves fewer than 512
+  Filler filler;
+  int64_t chunk = 0;
+  std::vector<AttnUnit> dec_units;
+  plan.dec_merges.clear();
+  plan.dec_parts = 0;
+  if (plan.mixed) {
+    const int64_t A = kvx::kDecodeChunkAlign;
+    chunk = split_keys > 0 ? split_keys : std::min<int64_t>(2048, std::max<int64_t>(512, one_keys / 512)) / A * A;
+    auto chunks_of = [&](int r) { return ceil_div((int64_t)b->prefix_lens[r] + 1, chunk); };
+    for (;; chunk *= 2) {  // keep the number of parts bounded
+      int64_t parts = 0;
+      for (int r = 0; r < b->num_reqs; r++)
+        if (b->extend_lens[r] == 1 && chunks_of(r) > 1) parts += chunks_of(r) * Hkv;
+      if (parts <= limits.decode) break;
+    }
+    for (int r = 0; r < b->num_reqs; r++) {
+      if (b->extend_lens[r] != 1) continue;
+      const int64_t L = (int64_t)b->prefix_lens[r] + 1, nc = chunks_of(r);
+      for (int32_t h = 0; h < Hkv; h++) {
+        if (nc > 1)
+          plan.dec_merges.push_back(
+              kvx::DecodeMerge{(int32_t)qo[(size_t)r], h, (int32_t)plan.dec_parts, (int32_t)nc});
+        for (int64_t c = 0; c < nc; c++) {
+          AttnUnit u;
+          u.qo_row0 = (int32_t)qo[(size_t)r];
+          u.q_pos0 = b->prefix_lens[r];
+          u.page_base = b->page_indptr[r];
+          u.key_begin = (int32_t)(c * chunk);
+          u.key_end = (int32_t)std::min<int64_t>(L, (c + 1) * chunk);
+          u.head_ntok = (h << 16) | kvx::kDecodeUnitFlag | 1;
+          u.part = nc > 1 ? (int32_t)plan.dec_parts++ : -1;
+          u.req = r;
+          dec_units.push_back(u);
+        }
+      }
+    }
+    std::stable_sort(dec_units.begin(), dec_units.end(), [](const AttnUnit& x, const AttnUnit& y) {
+      return x.key_end - x.key_begin > y.key_end - y.key_begin;
+    });
+    filler.units = ceil_div((int64_t)dec_units.size(), Hkv);
+    filler.cost = (double)(one_keys / BN) / (double)dec_units.size() * kDecodePerIter + kUnitCosts128.start;
+  }
+
+  int64_t split = split_keys > 0 ? split_keys : choose_split(tiles, Hkv, tile_tok, D, filler, limits.prefill);
   auto boundaries = [&](const Tile& t) { return split > 0 ? t.qpos0 / split : 0; };  // split, 2 split, ... <= qpos0
   while (split > 0) {  // keep the number of parts bounded
     int64_t parts = 0;
     for (const Tile& t : tiles)
       if (const int64_t nb = boundaries(t)) parts += nb + 1;
-    if (parts * Hkv <= max_parts) break;
+    if (parts * Hkv <= limits.prefill) break;
     split *= 2;
   }
 
@@ -536,6 +614,29 @@ int make_plan(const kvx_batch* b, const std::vector<int64_t>& qo, int32_t Hq, in
       std::stable_sort(v.begin(), v.end(), [](const Placed& x, const Placed& y) {
         return x.u.key_end - x.u.key_begin > y.u.key_end - y.u.key_begin;
       });
+  if (plan.mixed) {
+    for (int x = 0; x < kvx::kNumXcd; x++) {
+      std::vector<Placed>& pre = per_xcd[x];
+      std::vector<Placed> dec, all;
+      for (size_t i = (size_t)x; i < dec_units.size(); i += kvx::kNumXcd) dec.push_back(Placed{dec_units[i], 0});
+      // An XCD's units go to its four shader engines strictly in turn (unit k to engine
+      // k % 4, 8 CUs each) and in order, so that every engine must get both kinds alike:
+      // they alternate in groups of four.
+      constexpr size_t SE = 4;
+      double total = 0.0, done = 0.0;
+      for (const Placed& e : pre) total += (double)(e.u.key_end - e.u.key_begin);
+      size_t next = 0;
+      for (size_t i = 0; i < pre.size(); i++) {
+        all.push_back(pre[i]);
+        done += (double)(pre[i].u.key_end - pre[i].u.key_begin);
+        if (i % SE != SE - 1) continue;
+        const size_t due = (size_t)(kDecodeSpread * (double)dec.size() * done / total) / SE * SE;
+        while (next < due && next < dec.size()) all.push_back(dec[next++]);
+      }
+      while (next < dec.size()) all.push_back(dec[next++]);
+      pre.swap(all);
+    }
+  }
   size_t longest = 0;
   for (const auto& v : per_xcd) longest = std::max(longest, v.size());
   plan.units.clear();
@@ -547,8 +648,11 @@ int make_plan(const kvx_batch* b, const std::vector<int64_t>& qo, int32_t Hq, in
       if (i < per_xcd[x].size()) {
         const AttnUnit& u = per_xcd[x][i].u;
         plan.units.push_back(u);
-        plan.items.push_back(kvx_work_item{u.req, u.head_ntok >> 16, per_xcd[x][i].tok0, u.head_ntok & 0xFFFF,
-                                           u.key_begin, u.key_end, u.part, x});
+        const bool dec = (u.head_ntok & kvx::kDecodeUnitFlag) != 0;
+        // inspected part numbers are dense: decode parts follow the prefill parts
+        const int32_t part = dec && u.part >= 0 ? (int32_t)plan.n_parts + u.part : u.part;
+        plan.items.push_back(kvx_work_item{u.req, u.head_ntok >> 16, per_xcd[x][i].tok0, u.head_ntok & 0x7FFF,
+                                           u.key_begin, u.key_end, part, x});
       } else {
         AttnUnit pad{};
         pad.part = -1;
@@ -712,11 +816,13 @@ struct CallBuffers {
 };
 
 template <typename U, typename M>
-std::vector<uint8_t> plan_blob(const std::vector<U>& units, const std::vector<M>& merges) {
-  const size_t ub = units.size() * sizeof(U), mb = merges.size() * sizeof(M);
-  std::vector<uint8_t> blob(ub + mb);
+std::vector<uint8_t> plan_blob(const std::vector<U>& units, const std::vector<M>& merges,
+                               const std::vector<DecodeMerge>& dec_merges = {}) {
+  const size_t ub = units.size() * sizeof(U), mb = merges.size() * sizeof(M), db = dec_merges.size() * sizeof(DecodeMerge);
+  std::vector<uint8_t> blob(ub + mb + db);
   if (ub) std::memcpy(blob.data(), units.data(), ub);
   if (mb) std::memcpy(blob.data() + ub, merges.data(), mb);
+  if (db) std::memcpy(blob.data() + ub + mb, dec_merges.data(), db);
   return blob;
 }
 
@@ -1194,7 +1300,8 @@ int extend_attention_plan(const kvx_batch* batch, int32_t num_q_heads, int32_t n
       out_items = std::move(dp.items);
     } else {
       Plan plan;
-      if (int rc = make_plan(batch, qo, num_q_heads, num_kv_heads, head_dim, split_keys, kMaxParts, plan)) return rc;
+      if (int rc = make_plan(batch, qo, num_q_heads, num_kv_heads, head_dim, split_keys,
+                             PartLimits{kMaxParts, kMaxParts}, true, plan)) return rc;
       out_items = std::move(plan.items);
     }
   }
@@ -1234,20 +1341,29 @@ int kvx::attention_call(kvx_pool* pool, const kvx_batch* batch, const void* q, i
 
   const int D = pool->head_dim;
   const size_t part_bytes = (size_t)kvx::kTileRows * (D + 1) * sizeof(float);
+  const size_t dec_part_bytes = (size_t)kvx::kDecodeMaxGroup * (D + 1) * sizeof(float);
   Plan plan;
-  if (int rc = make_plan(batch, qo, num_q_heads, pool->num_kv_heads, D, pool->split_keys, buf.max_parts(part_bytes),
-                         plan))
-    return rc;
-  // one upload: units, then merges
-  const std::vector<uint8_t> blob = plan_blob(plan.units, plan.merges);
+  std::vector<uint8_t> blob;  // one upload: units, then merges, then the decode units' merges
+  for (const bool mixed : {true, false}) {
+    // in the fixed scratch, a mixed plan's decode parts have a quarter of the region
+    PartLimits lim{buf.max_parts(part_bytes), buf.max_parts(dec_part_bytes)};
+    if (fixed && mixed) lim = PartLimits{lim.prefill - (lim.prefill + 3) / 4, lim.decode / 4};
+    plan = Plan();
+    if (int rc = make_plan(batch, qo, num_q_heads, pool->num_kv_heads, D, pool->split_keys, lim, mixed, plan)) return rc;
+    if (fixed && mixed && !plan.mixed) continue;  // no decode units: the whole region for the rest
+    blob = plan_blob(plan.units, plan.merges, plan.dec_merges);
+    // a mixed plan has more units: what does not fit its region may fit without it
+    if (!(plan.mixed && fixed && blob.size() > fixed->plan_bytes)) break;
+  }
   if (int rc = buf.check_plan(blob.size())) return rc;
   if (int rc = use_device(pool)) return rc;
   if (validate_mode())
     if (int rc = check_page_ids(pool, batch, s)) return rc;
   if (int rc = buf.bind()) return rc;
   float* parts = nullptr;
-  if (plan.n_parts > 0)
-    if (int rc = buf.parts((size_t)plan.n_parts * part_bytes, s, &parts)) return rc;
+  if (plan.n_parts + plan.dec_parts > 0)
+    if (int rc = buf.parts((size_t)plan.n_parts * part_bytes + (size_t)plan.dec_parts * dec_part_bytes, s, &parts))
+      return rc;
   void* dev = nullptr;
   if (int rc = buf.upload(blob, s, &dev)) return rc;
 
@@ -1268,6 +1384,9 @@ int kvx::attention_call(kvx_pool* pool, const kvx_batch* batch, const void* q, i
   p.group = num_q_heads / pool->num_kv_heads;
   p.tile_tok = kvx::kTileRows / p.group;
   p.scale_log2 = sm_scale * 1.4426950408889634f;
+  p.mixed = plan.mixed ? 1 : 0;
+  p.d_part = plan.dec_parts ? parts + (size_t)plan.n_parts * (part_bytes / sizeof(float)) : nullptr;
+  p.d_lse = plan.dec_parts ? p.d_part + (size_t)plan.dec_parts * kvx::kDecodeMaxGroup * D : nullptr;
   hipError_t e = kvx::launch_extend_attention(p, (int64_t)plan.units.size(), D, pool->kv_dtype == KVX_KV_FP8_E4M3,
                                               pool->scaled_q != 0, s);
   if (e != hipSuccess) return hip_fail(e, "extend_attention kernel launch");
@@ -1282,6 +1401,19 @@ int kvx::attention_call(kvx_pool* pool, const kvx_batch* batch, const void* q, i
     m.group = p.group;
     e = kvx::launch_merge(m, (int64_t)plan.merges.size(), D, s);
     if (e != hipSuccess) return hip_fail(e, "merge kernel launch");
+  }
+  if (!plan.dec_merges.empty()) {
+    kvx::DecodeMergeParams m;
+    m.merges = (const DecodeMerge*)((const uint8_t*)dev + plan.units.size() * sizeof(AttnUnit) +
+                                    plan.merges.size() * sizeof(MergeUnit));
+    m.o_part = p.d_part;
+    m.lse_part = p.d_lse;
+    m.out = (uint16_t*)out;
+    m.lse = lse;
+    m.num_q_heads = num_q_heads;
+    m.group = p.group;
+    e = kvx::launch_decode_merge(m, (int64_t)plan.dec_merges.size(), D, s);
+    if (e != hipSuccess) return hip_fail(e, "decode merge kernel launch");
   }
   return buf.done(s);
 }

@@ -23,11 +23,15 @@ struct AttnUnit {
   int32_t page_base;  // offset of the request's page list in page_ids
   int32_t key_begin;  // multiple of kTileKeys
   int32_t key_end;    // exclusive; key_end <= key_begin marks a padding entry
-  int32_t head_ntok;  // (kv_head << 16) | tokens in the tile
+  int32_t head_ntok;  // (kv_head << 16) | tokens in the tile (kDecodeUnitFlag: a decode unit)
   int32_t part;       // -1: final result; else index of this part's partial result
   int32_t req;
 };
 static_assert(sizeof(AttnUnit) == 32, "AttnUnit is 32 bytes");
+// In head_ntok of a mixed batch's plan: the unit is one query token over a chunk of its
+// keys, run by the decode code (part then counts decode parts).
+constexpr int32_t kDecodeUnitFlag = 0x8000;
+static_assert(KVX_TILE_ROWS < kDecodeUnitFlag, "tokens of a tile stay below the flag");
 
 // Log-sum-exp merge of the parts of one split tile.
 struct MergeUnit {
@@ -62,6 +66,9 @@ struct AttnParams {
   int32_t group;          // Hq / Hkv
   int32_t tile_tok;       // tokens per tile = kTileRows / group
   float scale_log2;       // sm_scale * log2(e)
+  int32_t mixed;          // 1: the plan holds decode units too
+  float* d_part;          // fp32 [decode parts, kDecodeMaxGroup, D]
+  float* d_lse;           // fp32 [decode parts, kDecodeMaxGroup]
 };
 
 struct MergeParams {
@@ -232,6 +239,9 @@ int attention_call(kvx_pool* pool, const kvx_batch* batch, const void* q, int32_
 
 hipError_t launch_extend_attention(const AttnParams& p, int64_t n_units, int head_dim, bool fp8, bool scaled_q,
                                    hipStream_t stream);
+// launch_extend_attention of a plan that holds decode units (p.mixed)
+hipError_t launch_mixed_attention(const AttnParams& p, int64_t n_units, int head_dim, bool fp8, bool scaled_q,
+                                  hipStream_t stream);
 hipError_t launch_merge(const MergeParams& p, int64_t n_merges, int head_dim, hipStream_t stream);
 hipError_t launch_store_kv(const StoreParams& p, int64_t n_units, int head_dim, bool fp8,
                            hipStream_t stream);

@@ -5,6 +5,7 @@ CPU oracle with LSE, over pools whose unused slots hold NaN."""
 import numpy as np
 import pytest
 
+from paper_2609_32278_amd import kvx
 from paper_2609_32278_amd import workloads as wl
 from test_gpu_extend import _run_and_compare
 
@@ -24,3 +25,22 @@ def test_decode_at_the_edges_of_pages_and_key_steps(dt, hq, hkv, d, split):
     w = wl.make_custom(STEP_EDGES, [1] * len(STEP_EDGES), hq, hkv, d, kv_dtype=dt, seed=61)
     _run_and_compare(w, f"decode_edges_{dt}_{hq}_{hkv}_{d}_{split}", want_lse=True, fill=NAN_FILL[dt],
                      split_keys=split)
+
+
+# prefilling requests next to decoding ones: chunked and single-chunk decode prefixes, an
+# empty prefix (one key), a request with no suffix; enough one-token work for the mixed launch
+MIXED_P = [0, 4000, 9000, 33, 15000, 700, 2047, 2048, 5000, 12345]
+MIXED_E = [1, 1, 1, 130, 1, 40, 1, 1, 0, 1]
+
+
+@pytest.mark.parametrize("dt", [wl.KV_BF16, wl.KV_FP8_E4M3])
+@pytest.mark.parametrize("hq,hkv,d", [(32, 4, 128), (12, 6, 64), (64, 4, 64)])
+@pytest.mark.parametrize("split,scaled_q", [(0, False), (1024, False), (0, True)])
+def test_batches_that_mix_prefill_and_decode(dt, hq, hkv, d, split, scaled_q):
+    w = wl.make_custom(MIXED_P, MIXED_E, hq, hkv, d, kv_dtype=dt, seed=62)
+    b = kvx.Batch(w.prefix_lens, w.extend_lens, w.page_indptr, 0)
+    items = kvx.extend_attention_plan(b, hq, hkv, d, split)
+    assert (np.diff(np.unique(items["key_begin"][(items["req"] == 4)])) <= 2048).all()  # decode chunks
+    # decode units are always exact: compare with the exact attention at the standard gate
+    _run_and_compare(w, f"mixed_{dt}_{hq}_{hkv}_{d}_{split}_{int(scaled_q)}", want_lse=True, fill=NAN_FILL[dt],
+                     split_keys=split, scaled_q=scaled_q)
