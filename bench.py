@@ -102,8 +102,10 @@ def code_hash(path: str) -> str:
 def attn_source_hash(config: str = "llama8b") -> str:
     """Code hash of the attention (or decode) kernel source: committed counter
     summaries carry it, and their traffic is used only while it matches."""
-    name = "kvx_decode.hip" if is_decode(config) else "kvx_attn.hip"
-    return code_hash(os.path.join(ROOT, "paper_2609_32278_amd", "csrc", name))
+    names = ("kvx_decode.hip", "kvx_decode_unit.h") if is_decode(config) else ("kvx_attn.hip", "kvx_attn_kernels.h")
+    paths = [os.path.join(ROOT, "paper_2609_32278_amd", "csrc", n) for n in names]
+    code = "\n".join(code_only(open(p, encoding="utf-8").read()) for p in paths if os.path.exists(p))
+    return hashlib.sha256(code.encode()).hexdigest()[:16]
 
 
 def traffic_from_profiles(config: str):

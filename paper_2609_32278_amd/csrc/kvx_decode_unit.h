@@ -3,6 +3,8 @@
 // both.  Included once per .hip file, inside no namespace.
 #pragma once
 
+#include <type_traits>
+
 #include "kvx_internal.h"
 
 namespace kvx {
@@ -22,6 +24,20 @@ __device__ __forceinline__ uint32_t pack2(float a, float b) {
   v[0] = (__bf16)a;
   v[1] = (__bf16)b;
   return __builtin_bit_cast(uint32_t, v);
+}
+
+// A 16- or 8-byte load of pool data; NT: not kept in the caches (non-temporal).
+template <bool NT>
+__device__ __forceinline__ uint4 load16(const void* p) {
+  typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+  if constexpr (!NT) return *(const uint4*)p;
+  return __builtin_bit_cast(uint4, __builtin_nontemporal_load((const u32x4*)p));
+}
+template <bool NT>
+__device__ __forceinline__ uint2 load8(const void* p) {
+  typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+  if constexpr (!NT) return *(const uint2*)p;
+  return __builtin_bit_cast(uint2, __builtin_nontemporal_load((const u32x2*)p));
 }
 
 // max / sum over the four lane groups (lanes n, n+16, n+32, n+48) holding one row
@@ -106,7 +122,7 @@ struct PairRegs {
 };
 
 // One unit on NW waves; wave w takes page pairs w, w + NW, ...
-template <int D, int NW>
+template <int D, int NW, bool NT>
 __device__ __forceinline__ void decode_unit(const DecodeParams& p, const DecodeUnit& u, CombineShared<D, NW> sm) {
   constexpr int QS = D / 32;   // QK reduction steps
   constexpr int DB = D / 16;   // PV output blocks
@@ -146,16 +162,16 @@ __device__ __forceinline__ void decode_unit(const DecodeParams& p, const DecodeU
     const uint16_t* k = (const uint16_t*)p.k_pool;
 #pragma unroll
     for (int s = 0; s < QS; s++) {
-      r.ka[s] = *(const uint4*)(k + pa + n * D + 32 * s + 8 * g);
-      r.kb[s] = *(const uint4*)(k + pb + n * D + 32 * s + 8 * g);
+      r.ka[s] = load16<NT>(k + pa + n * D + 32 * s + 8 * g);
+      r.kb[s] = load16<NT>(k + pb + n * D + 32 * s + 8 * g);
     }
   };
   auto load_v = [&](size_t pa, size_t pb, PairRegs<D>& r) {
     const uint16_t* v = (const uint16_t*)p.v_pool;
 #pragma unroll
     for (int b = 0; b < DB; b++) {
-      r.va[b] = *(const uint2*)(v + pa + (16 * b + n) * kPageSize + 4 * g);
-      r.vb[b] = *(const uint2*)(v + pb + (16 * b + n) * kPageSize + 4 * g);
+      r.va[b] = load8<NT>(v + pa + (16 * b + n) * kPageSize + 4 * g);
+      r.vb[b] = load8<NT>(v + pb + (16 * b + n) * kPageSize + 4 * g);
     }
   };
 
@@ -274,7 +290,7 @@ struct QuadRegs {
   uint4 v[D / 16];     // V^T codes: all 16 slots of the lane's dim of page g
 };
 
-template <int D, int NW>
+template <int D, int NW, bool NT>
 __device__ __forceinline__ void decode_unit_fp8(const DecodeParams& p, const DecodeUnit& u, CombineShared<D, NW> sm) {
   constexpr int KS = D / 64;  // K loads per MFMA row block
   constexpr int DB = D / 16;  // PV output blocks
@@ -324,12 +340,12 @@ __device__ __forceinline__ void decode_unit_fp8(const DecodeParams& p, const Dec
 #pragma unroll
     for (int j = 0; j < 4; j++)
 #pragma unroll
-      for (int i = 0; i < KS; i++) r.k[j][i] = *(const uint4*)(src + 4 * j * D + 64 * i);
+      for (int i = 0; i < KS; i++) r.k[j][i] = load16<NT>(src + 4 * j * D + 64 * i);
   };
   auto load_v = [&](const ids_t& w, QuadRegs<D>& r) {
     const char* src = vbase + (uint64_t)pick(w, v_odd, v_high) * page_bytes;
 #pragma unroll
-    for (int b = 0; b < DB; b++) r.v[b] = *(const uint4*)(src + 256 * b);
+    for (int b = 0; b < DB; b++) r.v[b] = load16<NT>(src + 256 * b);
   };
 
   f32x4 o[DB];
@@ -339,8 +355,11 @@ __device__ __forceinline__ void decode_unit_fp8(const DecodeParams& p, const Dec
   const float scale = p.scale_log2 * p.k_scale[u.head];
 
   // Quad `quad` from r; its registers are refilled with quad `next` (if < n_quads) as
-  // soon as the products have read them.
-  auto compute = [&](int quad, int next, QuadRegs<D>& r) {
+  // soon as the products have read them.  TAIL: the quad reaches past key_end.  (A template
+  // flag and not a branch: masking the loaded registers in place inside the loop made
+  // the compiler reuse some of them too early.)
+  auto compute = [&](int quad, int next, QuadRegs<D>& r, auto tail_flag) {
+    constexpr bool TAIL = decltype(tail_flag)::value;
     const bool more = next < n_quads;  // uniform
     ids_t nx{};
     if (more) nx = ids_of(next);
@@ -359,8 +378,7 @@ __device__ __forceinline__ void decode_unit_fp8(const DecodeParams& p, const Dec
     }
     if (more) load_k(nx, r);
     const int key0 = u.key_begin + 64 * quad + 16 * g;  // slot 0 of the lane group's page
-    const bool tail = u.key_begin + 64 * (quad + 1) > u.key_end;  // uniform
-    if (tail) {
+    if constexpr (TAIL) {
 #pragma unroll
       for (int j = 0; j < 4; j++)
 #pragma unroll
@@ -393,24 +411,18 @@ __device__ __forceinline__ void decode_unit_fp8(const DecodeParams& p, const Dec
     }
     const bf16x8 pa = __builtin_bit_cast(bf16x8, make_uint4(pw[0], pw[1], pw[2], pw[3]));
     const bf16x8 pb = __builtin_bit_cast(bf16x8, make_uint4(pw[4], pw[5], pw[6], pw[7]));
-    if (tail) {  // zero V of keys past the end: unwritten slots may hold NaN codes
-      uint32_t mask[4];
+    uint32_t mask[4];  // zeroes V of keys past the end: unwritten slots may hold NaN codes
+    if constexpr (TAIL) {
 #pragma unroll
       for (int e = 0; e < 4; e++) {
         const int left = u.key_end - key0 - 4 * e;  // live slots of this dword
         mask[e] = left >= 4 ? 0xFFFFFFFFu : left <= 0 ? 0u : (1u << (8 * left)) - 1u;
       }
-#pragma unroll
-      for (int b = 0; b < DB; b++) {
-        r.v[b].x &= mask[0];
-        r.v[b].y &= mask[1];
-        r.v[b].z &= mask[2];
-        r.v[b].w &= mask[3];
-      }
     }
 #pragma unroll
     for (int b = 0; b < DB; b++) {
-      const uint4 c = r.v[b];
+      uint4 c = r.v[b];
+      if constexpr (TAIL) c = make_uint4(c.x & mask[0], c.y & mask[1], c.z & mask[2], c.w & mask[3]);
       o[b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, fp8x8_bf16(make_uint2(c.x, c.y))), pa,
                                                      o[b], 0, 0, 0);
       o[b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, fp8x8_bf16(make_uint2(c.z, c.w))), pb,
@@ -425,7 +437,10 @@ __device__ __forceinline__ void decode_unit_fp8(const DecodeParams& p, const Dec
     load_k(w, r);
     load_v(w, r);
   }
-  for (int j = wave; j < n_quads; j += NW) compute(j, j + NW, r);
+  const int n_full = (u.key_end - u.key_begin) / (4 * kPageSize);  // at most the last quad is not full
+  int j = wave;
+  for (; j < n_full; j += NW) compute(j, j + NW, r, std::false_type{});
+  if (j < n_quads) compute(j, j + NW, r, std::true_type{});
   combine_waves<D, NW>(p, u, sm, o, m_run, l_run, p.v_scale[u.head]);
 }
 

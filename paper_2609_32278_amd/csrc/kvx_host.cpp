@@ -887,6 +887,10 @@ int decode_attention(kvx_pool* pool, const kvx_batch* batch, const std::vector<i
   p.num_kv_heads = pool->num_kv_heads;
   p.group = num_q_heads / pool->num_kv_heads;
   p.scale_log2 = sm_scale * 1.4426950408889634f;
+  p.kv_bytes = 0;
+  for (int r = 0; r < batch->num_reqs; r++)
+    if (batch->extend_lens[r] == 1)
+      p.kv_bytes += 2 * ((int64_t)batch->prefix_lens[r] + 1) * pool->num_kv_heads * D * pool->elem_bytes;
   hipError_t e = kvx::launch_decode(p, (int64_t)plan.units.size(), D, pool->kv_dtype == KVX_KV_FP8_E4M3, s);
   if (e != hipSuccess) return hip_fail(e, "decode kernel launch");
   if (!plan.merges.empty()) {

@@ -202,6 +202,7 @@ struct DecodeParams {
   int32_t num_kv_heads;
   int32_t group;          // Hq / Hkv <= kDecodeMaxGroup
   float scale_log2;
+  int64_t kv_bytes;       // K and V bytes the batch reads
 };
 
 struct DecodeMergeParams {

@@ -4,7 +4,9 @@ CPU oracle with LSE, over pools whose unused slots hold NaN."""
 
 import numpy as np
 import pytest
+import torch
 
+from gpu_harness import DEV, GpuRun
 from paper_2609_32278_amd import kvx
 from paper_2609_32278_amd import workloads as wl
 from test_gpu_extend import _run_and_compare
@@ -44,3 +46,26 @@ def test_batches_that_mix_prefill_and_decode(dt, hq, hkv, d, split, scaled_q):
     # decode units are always exact: compare with the exact attention at the standard gate
     _run_and_compare(w, f"mixed_{dt}_{hq}_{hkv}_{d}_{split}_{int(scaled_q)}", want_lse=True, fill=NAN_FILL[dt],
                      split_keys=split, scaled_q=scaled_q)
+
+
+@pytest.mark.parametrize("dt,d", [(wl.KV_BF16, 128), (wl.KV_FP8_E4M3, 128), (wl.KV_BF16, 64), (wl.KV_FP8_E4M3, 64)])
+def test_decode_beyond_the_infinity_cache_gives_the_same_bits(dt, d):
+    """A decode batch that reads more than 256 MB streams its pages with non-temporal
+    loads: the same bits as each request by itself, at the same chunk length."""
+    per = 2 * 8 * d * (2 if dt == wl.KV_BF16 else 1)  # K/V bytes per token
+    n = 1 + (300 << 20) // (50000 * per)
+    P = [50000 + 7 * i for i in range(n)]
+    w = wl.make_custom(P, [1] * n, 32, 8, d, kv_dtype=dt, seed=63, placement="linear")
+    run = GpuRun(w, split_keys=4096)
+    try:
+        run.store()
+        whole = run.attend()
+        for r in (0, n - 1):
+            ids = torch.from_numpy(w.pages_of(r).copy()).to(DEV)
+            one = kvx.Batch([P[r]], [1], [0, len(ids)], ids)
+            out = torch.zeros_like(whole[r:r + 1])
+            kvx.extend_attention(run.pool, one, run.q[r:r + 1].contiguous(), 32, w.sm_scale, out)
+            torch.cuda.synchronize()
+            assert torch.equal(out.view(torch.int16), whole[r:r + 1].view(torch.int16)), r
+    finally:
+        run.close()
