@@ -135,7 +135,11 @@ struct RopeParams {
   int32_t num_kv_heads;
   int32_t rotary_dim;        // multiple of 16, <= D
   float norm_eps;
-  int32_t lg_heads;          // log2 of the Q or K heads per workgroup (set by the launcher)
+  // set by the launcher: log2 of the Q and of the K heads per workgroup, and whether one
+  // workgroup takes all heads of a page
+  int32_t lg_q;
+  int32_t lg_k;
+  int32_t whole_page;
   double rev_freq[kRopeMaxPlanes];  // plane rate in revolutions per position: f_j / (2 pi)
   StoreReqs reqs;                   // reqs.n > 0: the units come from here instead
 };

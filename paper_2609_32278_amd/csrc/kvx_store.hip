@@ -320,7 +320,8 @@ __device__ __forceinline__ uint4 pack_bf16x8(const float (&y)[8]) {
 }
 
 // Grid: x = the unit (a touched page), y = a group of heads: first the groups of
-// 1 << p.lg_heads Q heads, then those of K heads, then those of HB V heads.
+// 1 << p.lg_q Q heads, then those of 1 << p.lg_k K heads, then those of HB V heads.  With
+// p.whole_page, y = 0 takes them all, one after another, with the angles formed once.
 template <int D, bool FP8, bool INTERLEAVED>
 __global__ __launch_bounds__(kStoreThreads) void store_kv_rope_kernel(RopeParams p) {
   constexpr int CPR = D / 8;
@@ -336,11 +337,14 @@ __global__ __launch_bounds__(kStoreThreads) void store_kv_rope_kernel(RopeParams
   const int ntok = u.slot_end - u.slot_begin;
   const int Hq = p.num_q_heads, H = p.num_kv_heads;
   const int row0 = u.row_slot0 + u.slot_begin;  // first suffix row of the unit
-  const int lg = p.lg_heads, hpg = 1 << lg;
-  const int nq = (Hq + hpg - 1) >> lg, nk = (H + hpg - 1) >> lg;
+  const int nq = (Hq + (1 << p.lg_q) - 1) >> p.lg_q, nk = (H + (1 << p.lg_k) - 1) >> p.lg_k;
   const int y = blockIdx.y;
+  const bool whole = p.whole_page != 0;
+  bool have_angles = false;
 
   auto angles = [&]() {
+    if (have_angles) return;  // uniform
+    have_angles = true;
     const int planes = p.rotary_dim / 2;
     for (int e = threadIdx.x; e < ntok * planes; e += kStoreThreads) {
       const int s = u.slot_begin + e / planes, j = e % planes;
@@ -353,21 +357,21 @@ __global__ __launch_bounds__(kStoreThreads) void store_kv_rope_kernel(RopeParams
     __syncthreads();
   };
 
-  if (y < nq) {
-    const int h0 = y << lg, nh = Hq - h0 < hpg ? Hq - h0 : hpg;
+  if (y < nq || (whole && Hq > 0)) {
+    const int hpg = 1 << p.lg_q, h0 = whole ? 0 : y << p.lg_q, nh = Hq - h0 < hpg ? Hq - h0 : hpg;
     uint16_t* qo = p.q_out + (size_t)row0 * Hq * D;
-    rope_rows<D, INTERLEAVED>(p.q + (size_t)row0 * Hq * D, ntok, Hq, h0, nh, lg, u.slot_begin, sm.cs, p.q_norm,
+    rope_rows<D, INTERLEAVED>(p.q + (size_t)row0 * Hq * D, ntok, Hq, h0, nh, p.lg_q, u.slot_begin, sm.cs, p.q_norm,
                               p.norm_eps, p.rotary_dim, angles, [&](int tok, int hd, int cc, const float(&v)[8]) {
                                 *(uint4*)(qo + ((size_t)tok * Hq + hd) * D + cc * 8) = pack_bf16x8(v);
                               });
-    return;
+    if (!whole) return;
   }
   const int page = p.page_ids[u.page_pos];
-  if (y < nq + nk) {
-    const int h0 = (y - nq) << lg, nh = H - h0 < hpg ? H - h0 : hpg;
+  if (whole || y < nq + nk) {
+    const int hpg = 1 << p.lg_k, h0 = whole ? 0 : (y - nq) << p.lg_k, nh = H - h0 < hpg ? H - h0 : hpg;
     rope_rows<D, INTERLEAVED>(
-        p.k_ext + (size_t)row0 * H * D, ntok, H, h0, nh, lg, u.slot_begin, sm.cs, p.k_norm, p.norm_eps, p.rotary_dim,
-        angles, [&](int tok, int hd, int cc, const float(&v)[8]) {
+        p.k_ext + (size_t)row0 * H * D, ntok, H, h0, nh, p.lg_k, u.slot_begin, sm.cs, p.k_norm, p.norm_eps,
+        p.rotary_dim, angles, [&](int tok, int hd, int cc, const float(&v)[8]) {
           const size_t blk = ((size_t)page * H + hd) * (size_t)(kPageSize * D);
           const int slot = u.slot_begin + tok;
           if constexpr (FP8) {
@@ -380,32 +384,35 @@ __global__ __launch_bounds__(kStoreThreads) void store_kv_rope_kernel(RopeParams
             *(uint4*)((uint16_t*)p.k_pool + blk + (size_t)slot * D + cc * 8) = pack_bf16x8(v);
           }
         });
-    return;
+    if (!whole) return;
   }
 
   // V: HB heads staged in LDS at once and written as [dim][slot] columns
-  const int h0 = (y - nq - nk) * HB;
-  uint4 vx[PER];
+  for (int h0 = whole ? 0 : (y - nq - nk) * HB; h0 < H; h0 += HB) {
+    uint4 vx[PER];
 #pragma unroll
-  for (int j = 0; j < PER; j++) {
-    const int i = threadIdx.x + j * kStoreThreads;
-    const int hd = h0 + i / VCHUNKS, slot = (i % VCHUNKS) / CPR, cc = i % CPR;
-    vx[j] = make_uint4(0, 0, 0, 0);
-    if (hd < H && slot >= u.slot_begin && slot < u.slot_end)
-      vx[j] = *(const uint4*)(p.v_ext + ((size_t)(u.row_slot0 + slot) * H + hd) * D + cc * 8);
-  }
+    for (int j = 0; j < PER; j++) {
+      const int i = threadIdx.x + j * kStoreThreads;
+      const int hd = h0 + i / VCHUNKS, slot = (i % VCHUNKS) / CPR, cc = i % CPR;
+      vx[j] = make_uint4(0, 0, 0, 0);
+      if (hd < H && slot >= u.slot_begin && slot < u.slot_end)
+        vx[j] = *(const uint4*)(p.v_ext + ((size_t)(u.row_slot0 + slot) * H + hd) * D + cc * 8);
+    }
+    if (whole) __syncthreads();  // the angles (or the heads before) have been read
 #pragma unroll
-  for (int j = 0; j < PER; j++) {
-    const int i = threadIdx.x + j * kStoreThreads;
-    *(uint4*)(&sm.vs[i / VCHUNKS][(i % VCHUNKS) / CPR][(i % CPR) * 8]) = vx[j];
-  }
-  __syncthreads();
+    for (int j = 0; j < PER; j++) {
+      const int i = threadIdx.x + j * kStoreThreads;
+      *(uint4*)(&sm.vs[i / VCHUNKS][(i % VCHUNKS) / CPR][(i % CPR) * 8]) = vx[j];
+    }
+    __syncthreads();
 #pragma unroll
-  for (int hb = 0; hb < HB; hb++) {
-    const int hd = h0 + hb;
-    if (hd >= H) break;  // uniform
-    const size_t blk = ((size_t)page * H + hd) * (size_t)(kPageSize * D);
-    write_vt<D, FP8>(sm.vs[hb], p.v_pool, blk, u.slot_begin, u.slot_end, FP8 ? p.v_inv_scale[hd] : 1.0f);
+    for (int hb = 0; hb < HB; hb++) {
+      const int hd = h0 + hb;
+      if (hd >= H) break;  // uniform
+      const size_t blk = ((size_t)page * H + hd) * (size_t)(kPageSize * D);
+      write_vt<D, FP8>(sm.vs[hb], p.v_pool, blk, u.slot_begin, u.slot_end, FP8 ? p.v_inv_scale[hd] : 1.0f);
+    }
+    if (!whole) return;
   }
 }
 
@@ -499,18 +506,33 @@ hipError_t launch_store_kv(const StoreParams& p, int64_t n_units, int head_dim, 
   return hipGetLastError();
 }
 
-// log2 of the Q or K heads per rope workgroup.  Fewer heads give more workgroups,
-// more heads compute the unit's angles less often.  Measured (us per call, 4 / 8 / 16 /
+// Heads per rope workgroup, and the workgroups per page.  Fewer heads give more workgroups,
+// more heads compute the page's angles less often.  Measured (us per call, 4 / 8 / 16 /
 // 32 heads): 150 pages of 32+8 heads 16.4 / 17.1 / 20.9 / 31.8, 270 pages 24.6 / 22.5 /
 // 26.1 / 33.6, 1700 pages of 64+8 heads 255 / 241 / 237 / 246, 2048 pages of 32+8 heads
 // 180 / 169 / 157 / 169 -- so up to 2048 workgroups 4 heads, and never more than 16.
-static int rope_lg_heads(const RopeParams& p, int64_t n_units, int64_t& groups) {
+// Where all heads of a page are few, one workgroup takes them all once the pages alone fill
+// the chip several times: 11000 pages of 8+2 heads of 64 126 us (140 in groups), of 8+1 heads
+// of 128 192 us (208); 3000 pages 36.7 us (35.4) and 58.6 us (58.2).
+static int64_t rope_groups(RopeParams& p, int64_t n_units) {
+  auto log2_up = [](int n) {
+    int lg = 0;
+    while ((1 << lg) < n) lg++;
+    return lg;
+  };
+  const int Hq = p.num_q_heads, H = p.num_kv_heads;
+  p.whole_page = Hq + 2 * H <= 16 && n_units >= 4096;
+  p.lg_q = log2_up(Hq);
+  p.lg_k = log2_up(H);
+  if (p.whole_page) return 1;
   for (int lg = 2;; lg++) {
-    const int64_t hpg = (int64_t)1 << lg;
-    groups = (p.num_q_heads + hpg - 1) / hpg + (p.num_kv_heads + hpg - 1) / hpg +
-             (p.num_kv_heads + kRopeVHeads - 1) / kRopeVHeads;
+    // no group larger than the heads there are: its rows past them would idle
+    p.lg_q = Hq > 0 ? (lg < log2_up(Hq) ? lg : log2_up(Hq)) : 0;
+    p.lg_k = lg < log2_up(H) ? lg : log2_up(H);
+    const int64_t groups = (((int64_t)Hq + (1 << p.lg_q) - 1) >> p.lg_q) + (((int64_t)H + (1 << p.lg_k) - 1) >> p.lg_k) +
+                           (H + kRopeVHeads - 1) / kRopeVHeads;
     // a grid's y dimension is bounded by 65535 (tens of thousands of heads)
-    if (groups <= 65535 && (lg >= 4 || n_units * groups <= 2048)) return lg;
+    if (groups <= 65535 && (lg >= 4 || n_units * groups <= 2048)) return groups;
   }
 }
 
@@ -518,8 +540,7 @@ hipError_t launch_store_kv_rope(const RopeParams& params, int64_t n_units, int h
                                 hipStream_t stream) {
   if (n_units <= 0) return hipSuccess;
   RopeParams p = params;
-  int64_t groups = 0;
-  p.lg_heads = rope_lg_heads(p, n_units, groups);
+  const int64_t groups = rope_groups(p, n_units);
   dim3 grid((unsigned)n_units, (unsigned)groups), block(kStoreThreads);
 #define KVX_ROPE_LAUNCH(D, F, I) hipLaunchKernelGGL((store_kv_rope_kernel<D, F, I>), grid, block, 0, stream, p)
   if (head_dim == 128) {

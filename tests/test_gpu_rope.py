@@ -377,12 +377,15 @@ def test_full_size_llama8b_with_fused_rope():
     (3, 5, 5, wl.KV_BF16),        # 4 heads per workgroup, ragged last groups of Q, K and V heads
     (190, 40, 5, wl.KV_BF16),     # 8 heads per workgroup
     (260, 40, 5, wl.KV_FP8_E4M3),  # 16 heads per workgroup
+    (4100, 5, 5, wl.KV_BF16),      # one workgroup takes all heads of a page
+    (4100, 4, 6, wl.KV_FP8_E4M3),
+    (4100, 0, 5, wl.KV_BF16),      # K and V alone
 ])
 def test_head_groups_of_the_fused_store(pages, hq, hkv, kv_dtype):
     """The fused store splits a page's heads over workgroups (4, 8 or 16 per group by
     the batch's size): head counts that leave a ragged last group, at each size."""
-    CASES["head_groups"] = ([7], [16 * pages - 9], hq, hkv, 128, kv_dtype, wl.RopeSpec(1e6, 128, R.HALF, True))
+    CASES["head_groups"] = ([7], [16 * pages - 9], max(hq, hkv), hkv, 128, kv_dtype, wl.RopeSpec(1e6, 128, R.HALF, True))
     try:
-        _check_store("head_groups", seed=5)
+        _check_store("head_groups", seed=5, with_q=hq > 0)
     finally:
         del CASES["head_groups"]
