@@ -15,7 +15,15 @@ template <int D>
 __global__ __launch_bounds__(256) void merge_kernel(MergeParams p) {
   constexpr int UNROLL = 8;
   constexpr int DB = Geom<D>::DB;
-  const MergeUnit mu = p.merges[blockIdx.x];
+  MergeUnit mu;
+  if (p.plan.n > 0) {
+    const int h = blockIdx.x % p.plan.heads;
+    mu = p.plan.merge[blockIdx.x / p.plan.heads];
+    mu.head_ntok += h << 16;
+    mu.part0 += h * mu.nparts;
+  } else {
+    mu = p.merges[blockIdx.x];
+  }
   const int kv_head = mu.head_ntok >> 16;
   const int ntok = mu.head_ntok & 0xFFFF;
   const int blk = (int)blockIdx.y / DB, b = (int)blockIdx.y % DB;
@@ -62,9 +70,48 @@ __global__ __launch_bounds__(256) void merge_kernel(MergeParams p) {
 
 }  // namespace
 
+struct WritePlanParams {
+  AttnUnit* out;
+  int32_t n;  // units to write
+  InlinePlan<AttnUnit> plan;
+};
+static_assert(sizeof(WritePlanParams) <= 4096, "kernel arguments");
+
+// Write the units the kernel arguments stand for to the plan buffer (see InlinePlan).
+__global__ __launch_bounds__(256) void write_plan_kernel(WritePlanParams p) {
+  const int i = blockIdx.x * 256 + threadIdx.x;
+  if (i >= p.n) return;
+  const int h = i % p.plan.heads;
+  AttnUnit u = p.plan.unit[i / p.plan.heads];
+  u.head_ntok += h << 16;
+  u.part = u.part < 0 ? -1 : u.part + h * u.req;
+  p.out[i] = u;
+}
+
+static hipError_t write_plan(const AttnParams& p, hipStream_t stream) {
+  const int heads = p.plan_heads;
+  for (int64_t done = 0; done < p.plan_units; done += (int64_t)kInlineUnits * heads) {
+    WritePlanParams w;
+    w.out = const_cast<AttnUnit*>(p.units) + done;
+    const int64_t left = p.plan_units - done, most = (int64_t)kInlineUnits * heads;
+    w.n = (int32_t)(left < most ? left : most);
+    w.plan.heads = heads;
+    w.plan.n = w.n / heads;
+    for (int e = 0; e < w.plan.n; e++) {
+      const AttnUnit* u = p.host_units + done + (int64_t)e * heads;
+      w.plan.unit[e] = u[0];
+      w.plan.unit[e].req = heads > 1 && u[0].part >= 0 ? u[1].part - u[0].part : 0;
+    }
+    hipLaunchKernelGGL(write_plan_kernel, dim3((unsigned)((w.n + 255) / 256)), dim3(256), 0, stream, w);
+  }
+  return hipGetLastError();
+}
+
 hipError_t launch_extend_attention(const AttnParams& p, int64_t n_units, int head_dim, bool fp8, bool scaled_q,
                                    hipStream_t stream) {
   if (n_units <= 0) return hipSuccess;
+  if (p.plan_units > 0)
+    if (hipError_t e = write_plan(p, stream); e != hipSuccess) return e;
   if (p.mixed) return launch_mixed_attention(p, n_units, head_dim, fp8, scaled_q, stream);
   launch_attn<false>(p, n_units, head_dim, fp8, scaled_q, stream);
   return hipGetLastError();

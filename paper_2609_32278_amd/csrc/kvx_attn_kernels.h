@@ -550,7 +550,7 @@ __device__ __forceinline__ bool run_decode_unit(const AttnParams& p, uint8_t* o_
   u.key_end = w[4];
   u.head = head_ntok >> 16;
   u.part = w[6];
-  DecodeParams d;
+  DecodeArgs d;
   d.q = p.q;
   d.out = p.out;
   d.lse = p.lse;
@@ -565,8 +565,6 @@ __device__ __forceinline__ bool run_decode_unit(const AttnParams& p, uint8_t* o_
   d.num_kv_heads = p.num_kv_heads;
   d.group = p.group;
   d.scale_log2 = p.scale_log2;
-  d.units = nullptr;
-  d.kv_bytes = 0;
   const decode::CombineShared<D, kWaves> sm{(float*)o_lds, (float*)ml_lds, (float*)ml_lds + kWaves * decode::kRows};
   if constexpr (FP8) decode::decode_unit_fp8<D, kWaves, false>(d, u, sm);
   else decode::decode_unit<D, kWaves, false>(d, u, sm);

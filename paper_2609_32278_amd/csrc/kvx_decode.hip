@@ -33,14 +33,22 @@ constexpr int kWaves = kDecodeThreads / 64;
 
 // The work item of this workgroup (scalar loads: everything derived stays uniform).
 __device__ __forceinline__ DecodeUnit unit_of(const DecodeParams& p) {
+  using decode::const_i32_ptr;
+  const_i32_ptr w = (const_i32_ptr)(p.units + blockIdx.x);
+  int h = 0;
+  if (p.plan.n > 0) {  // in the kernel arguments
+    w = (const_i32_ptr)((const __attribute__((address_space(4))) char*)__builtin_amdgcn_kernarg_segment_ptr() +
+                        offsetof(DecodeParams, plan.unit)) +
+        (blockIdx.x / p.plan.heads) * (sizeof(DecodeUnit) / 4);
+    h = blockIdx.x % p.plan.heads;
+  }
   DecodeUnit u;
-  const decode::const_i32_ptr w = (decode::const_i32_ptr)(p.units + blockIdx.x);
   u.qo_row = w[0];
   u.page_base = w[1];
   u.key_begin = w[2];
   u.key_end = w[3];
-  u.head = w[4];
-  u.part = w[5];
+  u.head = w[4] + h;
+  u.part = w[5] < 0 ? -1 : w[5] + h * w[6];
   return u;
 }
 
@@ -49,8 +57,8 @@ __global__ __launch_bounds__(kDecodeThreads, 2) void decode_kernel(DecodeParams 
   __shared__ float o[kWaves * kRows * D], m[kWaves * kRows], l[kWaves * kRows];
   const decode::CombineShared<D, kWaves> sm{o, m, l};
   const DecodeUnit u = unit_of(p);
-  if constexpr (FP8) decode::decode_unit_fp8<D, kWaves, NT>(p, u, sm);
-  else decode::decode_unit<D, kWaves, NT>(p, u, sm);
+  if constexpr (FP8) decode::decode_unit_fp8<D, kWaves, NT>(p.a, u, sm);
+  else decode::decode_unit<D, kWaves, NT>(p.a, u, sm);
 }
 
 // Combine the parts of a split decode key range: o = sum_p e^{lse_p - M} o_p / sum_p e^{lse_p - M}.
@@ -66,7 +74,15 @@ __global__ __launch_bounds__(256) void decode_merge_kernel(DecodeMergeParams p) 
   constexpr int UNROLL = 4;        // parts in flight per group
   __shared__ float sm_m[PG], sm_w[PG];
   __shared__ f32x4 sm_o[PG][C4];
-  const DecodeMerge mu = p.merges[blockIdx.x];
+  DecodeMerge mu;
+  if (p.plan.n > 0) {
+    const int h = blockIdx.x % p.plan.heads;
+    mu = p.plan.merge[blockIdx.x / p.plan.heads];
+    mu.head += h;
+    mu.part0 += h * mu.nparts;
+  } else {
+    mu = p.merges[blockIdx.x];
+  }
   const int row = blockIdx.y;
   const int c = threadIdx.x % C4, pg = threadIdx.x / C4;
   const float* lse = p.lse_part + (size_t)mu.part0 * kRows + row;

@@ -71,7 +71,7 @@ struct CombineShared {
 // Lane (n, g) holds dims 16 b + 4 g + i of row n, relative to its row maximum m_run
 // (log2 units), and the part l_run of the row sum over its own keys.
 template <int D, int NW>
-__device__ __forceinline__ void combine_waves(const DecodeParams& p, const DecodeUnit& u, CombineShared<D, NW> sm,
+__device__ __forceinline__ void combine_waves(const DecodeArgs& p, const DecodeUnit& u, CombineShared<D, NW> sm,
                                               const f32x4 (&o)[D / 16], float m_run, float l_run, float vscale) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int n = lane & 15, g = lane >> 4, G = p.group;
@@ -123,7 +123,7 @@ struct PairRegs {
 
 // One unit on NW waves; wave w takes page pairs w, w + NW, ...
 template <int D, int NW, bool NT>
-__device__ __forceinline__ void decode_unit(const DecodeParams& p, const DecodeUnit& u, CombineShared<D, NW> sm) {
+__device__ __forceinline__ void decode_unit(const DecodeArgs& p, const DecodeUnit& u, CombineShared<D, NW> sm) {
   constexpr int QS = D / 32;   // QK reduction steps
   constexpr int DB = D / 16;   // PV output blocks
   constexpr int PAGE_ELEMS = kPageSize * D;
@@ -291,7 +291,7 @@ struct QuadRegs {
 };
 
 template <int D, int NW, bool NT>
-__device__ __forceinline__ void decode_unit_fp8(const DecodeParams& p, const DecodeUnit& u, CombineShared<D, NW> sm) {
+__device__ __forceinline__ void decode_unit_fp8(const DecodeArgs& p, const DecodeUnit& u, CombineShared<D, NW> sm) {
   constexpr int KS = D / 64;  // K loads per MFMA row block
   constexpr int DB = D / 16;  // PV output blocks
   const int lane = threadIdx.x & 63;

@@ -97,7 +97,6 @@ struct Staging {
   // The caller records done() on the stream after the kernels that read it.
   int upload(const void* src, size_t bytes, hipStream_t stream, void** out) {
     if (!ev) KVX_HIP(hipEventCreateWithFlags(&ev, hipEventDisableTiming));
-    if (!used) KVX_HIP(hipEventCreateWithFlags(&used, hipEventDisableTiming));
     if (pending) {
       KVX_HIP(hipEventSynchronize(ev));
       pending = false;
@@ -109,6 +108,17 @@ struct Staging {
       KVX_HIP(hipHostMalloc(&host, cap, hipHostMallocDefault));
       host_cap = cap;
     }
+    if (int rc = reserve(bytes, stream, out)) return rc;
+    std::memcpy(host, src, bytes);
+    KVX_HIP(hipMemcpyAsync(dev, host, bytes, hipMemcpyHostToDevice, stream));
+    KVX_HIP(hipEventRecord(ev, stream));
+    pending = true;
+    return KVX_OK;
+  }
+
+  // Device memory of at least `bytes`, for a kernel on `stream` to fill (as upload's).
+  int reserve(size_t bytes, hipStream_t stream, void** out) {
+    if (!used) KVX_HIP(hipEventCreateWithFlags(&used, hipEventDisableTiming));
     if (bytes > dev_cap) {
       if (dev) {
         // earlier kernels (on any stream) that read the old buffer precede `used`
@@ -121,10 +131,6 @@ struct Staging {
       KVX_HIP(hipMallocAsync(&dev, cap, stream));
       dev_cap = cap;
     }
-    std::memcpy(host, src, bytes);
-    KVX_HIP(hipMemcpyAsync(dev, host, bytes, hipMemcpyHostToDevice, stream));
-    KVX_HIP(hipEventRecord(ev, stream));
-    pending = true;
     *out = dev;
     return KVX_OK;
   }
@@ -722,20 +728,24 @@ int make_decode_plan(const kvx_batch* b, const std::vector<int64_t>& qo, int32_t
     if (b->extend_lens[r] != 1) continue;
     const int64_t L = (int64_t)b->prefix_lens[r] + 1;
     const int64_t nc = (L + chunk - 1) / chunk;
-    for (int32_t h = 0; h < Hkv; h++) {
-      const int64_t part0 = plan.n_parts;
-      for (int64_t c = 0; c < nc; c++) {
+    const int64_t part0 = plan.n_parts;
+    for (int64_t c = 0; c < nc; c++) {
+      for (int32_t h = 0; h < Hkv; h++) {  // heads side by side (see InlinePlan)
         DecodeUnit u{};
         u.qo_row = (int32_t)qo[(size_t)r];
         u.page_base = b->page_indptr[r];
         u.key_begin = (int32_t)(c * chunk);
         u.key_end = (int32_t)std::min<int64_t>(L, (c + 1) * chunk);
         u.head = h;
-        u.part = nc > 1 ? (int32_t)plan.n_parts++ : -1;
+        u.part = nc > 1 ? (int32_t)(part0 + h * nc + c) : -1;
         u.req = r;
         plan.units.push_back(u);
       }
-      if (nc > 1) plan.merges.push_back(DecodeMerge{(int32_t)qo[(size_t)r], h, (int32_t)part0, (int32_t)nc});
+    }
+    if (nc > 1) {
+      for (int32_t h = 0; h < Hkv; h++)
+        plan.merges.push_back(DecodeMerge{(int32_t)qo[(size_t)r], h, (int32_t)(part0 + h * nc), (int32_t)nc});
+      plan.n_parts += nc * Hkv;
     }
   }
   std::stable_sort(plan.units.begin(), plan.units.end(), [](const DecodeUnit& x, const DecodeUnit& y) {
@@ -799,6 +809,14 @@ struct CallBuffers {
     *out = (float*)pool->parts.ptr;
     return KVX_OK;
   }
+  // Room for a plan that a kernel writes.
+  int reserve(size_t bytes, hipStream_t s, void** out) {
+    if (fixed) {
+      *out = base;
+      return KVX_OK;
+    }
+    return pool->st_attn.reserve(bytes, s, out);
+  }
   int upload(const std::vector<uint8_t>& blob, hipStream_t s, void** out) {
     if (fixed) {
       // pageable source: the copy is staged before the call returns
@@ -808,12 +826,60 @@ struct CallBuffers {
     }
     return pool->st_attn.upload(blob.data(), blob.size(), s, out);
   }
-  int done(hipStream_t s) {
+  // staged: the call's kernels read the staging buffer
+  int done(hipStream_t s, bool staged) {
     if (fixed) return KVX_OK;
-    if (int rc = pool->st_attn.done(s)) return rc;
+    if (staged)
+      if (int rc = pool->st_attn.done(s)) return rc;
     return pool->parts.done(s);
   }
 };
+
+void add_head(AttnUnit& u, int32_t h) { u.head_ntok += h << 16; }
+void add_head(DecodeUnit& u, int32_t h) { u.head += h; }
+
+// Units per entry of a small plan in kernel arguments (see InlinePlan): 8 if every group of
+// eight differs in its KV heads and parts alone, else 1; 0 for a plan of more than
+// `launches` argument blocks.
+template <typename U>
+int32_t inline_heads(const std::vector<U>& units, size_t launches) {
+  constexpr int32_t H = kvx::kNumXcd;
+  const size_t most = launches * kvx::kInlineUnits;
+  if (units.size() > most * H) return 0;
+  bool grouped = units.size() % H == 0;
+  for (size_t i = 0; grouped && i < units.size(); i += H) {
+    const int32_t part = units[i].part, stride = part < 0 ? 0 : units[i + 1].part - part;
+    for (int32_t h = 1; grouped && h < H; h++) {
+      U x = units[i];
+      add_head(x, h);
+      x.part = part < 0 ? -1 : part + h * stride;
+      grouped = std::memcmp(&x, &units[i + (size_t)h], sizeof(U)) == 0;
+    }
+  }
+  return grouped ? H : units.size() <= most ? 1 : 0;
+}
+
+bool inline_units(const std::vector<DecodeUnit>& units, kvx::InlinePlan<DecodeUnit>& out) {
+  out.n = 0;
+  out.heads = inline_heads(units, 1);
+  if (out.heads == 0) return false;
+  for (size_t i = 0; i < units.size(); i += (size_t)out.heads) {
+    DecodeUnit e = units[i];
+    e.req = out.heads > 1 && e.part >= 0 ? units[i + 1].part - e.part : 0;
+    out.unit[out.n++] = e;
+  }
+  return true;
+}
+
+// The same for its merges, which go tile by tile (request by request) with all KV heads.
+template <typename M>
+bool inline_merges(const std::vector<M>& merges, int32_t Hkv, kvx::InlineMerges<M>& out) {
+  out.n = 0;
+  if (merges.size() > (size_t)kvx::kInlineMerges * Hkv) return false;
+  out.heads = Hkv;
+  for (size_t i = 0; i < merges.size(); i += (size_t)Hkv) out.merge[out.n++] = merges[i];
+  return true;
+}
 
 template <typename U, typename M>
 std::vector<uint8_t> plan_blob(const std::vector<U>& units, const std::vector<M>& merges,
@@ -860,7 +926,14 @@ int decode_attention(kvx_pool* pool, const kvx_batch* batch, const std::vector<i
   if (int rc = make_decode_plan(batch, qo, pool->num_kv_heads, pool->split_keys,
                                 buf.max_parts((size_t)R * (D + 1) * sizeof(float)), plan))
     return rc;
-  const std::vector<uint8_t> blob = plan_blob(plan.units, plan.merges);
+  kvx::DecodeParams dp;
+  kvx::DecodeMergeParams m;
+  const bool in_args = inline_merges(plan.merges, pool->num_kv_heads, m.plan) && inline_units(plan.units, dp.plan);
+  std::vector<uint8_t> blob;
+  if (!in_args) {
+    dp.plan.n = m.plan.n = 0;
+    blob = plan_blob(plan.units, plan.merges);
+  }
   if (int rc = buf.check_plan(blob.size())) return rc;
   if (int rc = use_device(pool)) return rc;
   if (validate_mode())
@@ -870,15 +943,16 @@ int decode_attention(kvx_pool* pool, const kvx_batch* batch, const std::vector<i
   if (plan.n_parts > 0)
     if (int rc = buf.parts((size_t)plan.n_parts * R * (D + 1) * sizeof(float), s, &parts)) return rc;
   void* dev = nullptr;
-  if (int rc = buf.upload(blob, s, &dev)) return rc;
-  kvx::DecodeParams p;
+  if (!in_args)
+    if (int rc = buf.upload(blob, s, &dev)) return rc;
+  kvx::DecodeArgs& p = dp.a;
   p.q = (const uint16_t*)q;
   p.out = (uint16_t*)out;
   p.lse = lse;
   p.k_pool = pool->k;
   p.v_pool = pool->v;
   p.page_ids = batch->page_ids;
-  p.units = (const DecodeUnit*)dev;
+  dp.units = (const DecodeUnit*)dev;
   p.o_part = plan.n_parts ? parts : nullptr;
   p.lse_part = plan.n_parts ? parts + (size_t)plan.n_parts * R * D : nullptr;
   p.k_scale = pool->scales_d;
@@ -887,14 +961,13 @@ int decode_attention(kvx_pool* pool, const kvx_batch* batch, const std::vector<i
   p.num_kv_heads = pool->num_kv_heads;
   p.group = num_q_heads / pool->num_kv_heads;
   p.scale_log2 = sm_scale * 1.4426950408889634f;
-  p.kv_bytes = 0;
+  dp.kv_bytes = 0;
   for (int r = 0; r < batch->num_reqs; r++)
     if (batch->extend_lens[r] == 1)
-      p.kv_bytes += 2 * ((int64_t)batch->prefix_lens[r] + 1) * pool->num_kv_heads * D * pool->elem_bytes;
-  hipError_t e = kvx::launch_decode(p, (int64_t)plan.units.size(), D, pool->kv_dtype == KVX_KV_FP8_E4M3, s);
+      dp.kv_bytes += 2 * ((int64_t)batch->prefix_lens[r] + 1) * pool->num_kv_heads * D * pool->elem_bytes;
+  hipError_t e = kvx::launch_decode(dp, (int64_t)plan.units.size(), D, pool->kv_dtype == KVX_KV_FP8_E4M3, s);
   if (e != hipSuccess) return hip_fail(e, "decode kernel launch");
   if (!plan.merges.empty()) {
-    kvx::DecodeMergeParams m;
     m.merges = (const DecodeMerge*)((const uint8_t*)dev + plan.units.size() * sizeof(DecodeUnit));
     m.o_part = p.o_part;
     m.lse_part = p.lse_part;
@@ -905,7 +978,7 @@ int decode_attention(kvx_pool* pool, const kvx_batch* batch, const std::vector<i
     e = kvx::launch_decode_merge(m, (int64_t)plan.merges.size(), D, s);
     if (e != hipSuccess) return hip_fail(e, "decode merge kernel launch");
   }
-  return buf.done(s);
+  return buf.done(s, !in_args);
 }
 
 }  // namespace
@@ -1347,6 +1420,9 @@ int kvx::attention_call(kvx_pool* pool, const kvx_batch* batch, const void* q, i
   const size_t part_bytes = (size_t)kvx::kTileRows * (D + 1) * sizeof(float);
   const size_t dec_part_bytes = (size_t)kvx::kDecodeMaxGroup * (D + 1) * sizeof(float);
   Plan plan;
+  kvx::AttnParams p;
+  kvx::MergeParams m;
+  bool in_args = false;
   std::vector<uint8_t> blob;  // one upload: units, then merges, then the decode units' merges
   for (const bool mixed : {true, false}) {
     // in the fixed scratch, a mixed plan's decode parts have a quarter of the region
@@ -1355,11 +1431,17 @@ int kvx::attention_call(kvx_pool* pool, const kvx_batch* batch, const void* q, i
     plan = Plan();
     if (int rc = make_plan(batch, qo, num_q_heads, pool->num_kv_heads, D, pool->split_keys, lim, mixed, plan)) return rc;
     if (fixed && mixed && !plan.mixed) continue;  // no decode units: the whole region for the rest
+    // at most three launches that write the units: a copy through the staging buffer costs
+    // a small call about 15 us, a launch about 3
+    p.plan_heads = plan.mixed || !inline_merges(plan.merges, pool->num_kv_heads, m.plan) ? 0 : inline_heads(plan.units, 3);
+    in_args = p.plan_heads > 0;
+    if (in_args) break;
+    m.plan.n = 0;
     blob = plan_blob(plan.units, plan.merges, plan.dec_merges);
     // a mixed plan has more units: what does not fit its region may fit without it
     if (!(plan.mixed && fixed && blob.size() > fixed->plan_bytes)) break;
   }
-  if (int rc = buf.check_plan(blob.size())) return rc;
+  if (int rc = buf.check_plan(in_args ? plan.units.size() * sizeof(AttnUnit) : blob.size())) return rc;
   if (int rc = use_device(pool)) return rc;
   if (validate_mode())
     if (int rc = check_page_ids(pool, batch, s)) return rc;
@@ -1369,9 +1451,10 @@ int kvx::attention_call(kvx_pool* pool, const kvx_batch* batch, const void* q, i
     if (int rc = buf.parts((size_t)plan.n_parts * part_bytes + (size_t)plan.dec_parts * dec_part_bytes, s, &parts))
       return rc;
   void* dev = nullptr;
-  if (int rc = buf.upload(blob, s, &dev)) return rc;
+  if (int rc = in_args ? buf.reserve(plan.units.size() * sizeof(AttnUnit), s, &dev) : buf.upload(blob, s, &dev)) return rc;
+  p.host_units = plan.units.data();
+  p.plan_units = in_args ? (int32_t)plan.units.size() : 0;
 
-  kvx::AttnParams p;
   p.q = (const uint16_t*)q;
   p.out = (uint16_t*)out;
   p.lse = lse;
@@ -1395,7 +1478,6 @@ int kvx::attention_call(kvx_pool* pool, const kvx_batch* batch, const void* q, i
                                               pool->scaled_q != 0, s);
   if (e != hipSuccess) return hip_fail(e, "extend_attention kernel launch");
   if (!plan.merges.empty()) {
-    kvx::MergeParams m;
     m.merges = (const MergeUnit*)((const uint8_t*)dev + plan.units.size() * sizeof(AttnUnit));
     m.o_part = p.o_part;
     m.lse_part = p.lse_part;
@@ -1407,17 +1489,18 @@ int kvx::attention_call(kvx_pool* pool, const kvx_batch* batch, const void* q, i
     if (e != hipSuccess) return hip_fail(e, "merge kernel launch");
   }
   if (!plan.dec_merges.empty()) {
-    kvx::DecodeMergeParams m;
-    m.merges = (const DecodeMerge*)((const uint8_t*)dev + plan.units.size() * sizeof(AttnUnit) +
-                                    plan.merges.size() * sizeof(MergeUnit));
-    m.o_part = p.d_part;
-    m.lse_part = p.d_lse;
-    m.out = (uint16_t*)out;
-    m.lse = lse;
-    m.num_q_heads = num_q_heads;
-    m.group = p.group;
-    e = kvx::launch_decode_merge(m, (int64_t)plan.dec_merges.size(), D, s);
+    kvx::DecodeMergeParams dm;
+    dm.plan.n = 0;
+    dm.merges = (const DecodeMerge*)((const uint8_t*)dev + plan.units.size() * sizeof(AttnUnit) +
+                                     plan.merges.size() * sizeof(MergeUnit));
+    dm.o_part = p.d_part;
+    dm.lse_part = p.d_lse;
+    dm.out = (uint16_t*)out;
+    dm.lse = lse;
+    dm.num_q_heads = num_q_heads;
+    dm.group = p.group;
+    e = kvx::launch_decode_merge(dm, (int64_t)plan.dec_merges.size(), D, s);
     if (e != hipSuccess) return hip_fail(e, "decode merge kernel launch");
   }
-  return buf.done(s);
+  return buf.done(s, true);
 }

@@ -49,6 +49,26 @@ struct StoreUnit {
   int32_t slot_end;
 };
 
+// Small plans travel in kernel arguments instead of through a copy (whose start and end
+// cost a small call more than its kernels).  An entry stands for `heads` units: unit i
+// is entry i / heads, with i % heads added to its KV head and (i % heads) times a stride
+// (kept in `req`, which no kernel uses) to its part.  heads is 8 where groups of eight units
+// differ in nothing else (eight KV heads side by side on the eight XCDs), else 1.
+constexpr int kInlineUnits = 110;   // 32-byte units: the arguments stay below 4 KiB
+constexpr int kInlineMerges = 220;  // 16-byte merges, one entry for all KV heads of a tile
+template <typename U>
+struct InlinePlan {
+  int32_t n;      // entries; 0: the units are uploaded
+  int32_t heads;  // units per entry
+  U unit[kInlineUnits];
+};
+template <typename M>
+struct InlineMerges {
+  int32_t n;      // entries; 0: the merges are uploaded
+  int32_t heads;  // merges per entry: KV heads h = 0 .. heads - 1, parts h * nparts further on
+  M merge[kInlineMerges];
+};
+
 struct AttnParams {
   const uint16_t* q;      // bf16 [T, Hq, D]
   uint16_t* out;          // bf16 [T, Hq, D]
@@ -69,6 +89,12 @@ struct AttnParams {
   int32_t mixed;          // 1: the plan holds decode units too
   float* d_part;          // fp32 [decode parts, kDecodeMaxGroup, D]
   float* d_lse;           // fp32 [decode parts, kDecodeMaxGroup]
+  // For the launcher: plan_units > 0 units in host memory, which it writes to `units` by a
+  // kernel of its own (the attention kernels read their units from there only: their main
+  // loop has no scalar register to spare for choosing between two places).
+  const AttnUnit* host_units;
+  int32_t plan_heads;  // as InlinePlan::heads
+  int32_t plan_units;
 };
 
 struct MergeParams {
@@ -79,7 +105,9 @@ struct MergeParams {
   float* lse;
   int32_t num_q_heads;
   int32_t group;
+  InlineMerges<MergeUnit> plan;  // plan.n > 0: the merges
 };
+static_assert(sizeof(MergeParams) <= 4096, "kernel arguments");
 
 // The requests of a small store batch, passed by value in the kernel arguments so
 // that no unit list is uploaded: request r's pages are the workgroups
@@ -190,14 +218,13 @@ struct DecodeMerge {
   int32_t nparts;
 };
 
-struct DecodeParams {
+struct DecodeArgs {
   const uint16_t* q;      // bf16 [T, Hq, D]
   uint16_t* out;          // bf16 [T, Hq, D]
   float* lse;             // fp32 [T, Hq] or null
   const void* k_pool;     // [page][kv_head][slot][D], bf16 or fp8
   const void* v_pool;     // [page][kv_head][D][slot]
   const int32_t* page_ids;
-  const DecodeUnit* units;
   float* o_part;          // fp32 [parts, kDecodeMaxGroup, D]
   float* lse_part;        // fp32 [parts, kDecodeMaxGroup]
   const float* k_scale;   // fp8 pool: device [Hkv]
@@ -206,8 +233,15 @@ struct DecodeParams {
   int32_t num_kv_heads;
   int32_t group;          // Hq / Hkv <= kDecodeMaxGroup
   float scale_log2;
-  int64_t kv_bytes;       // K and V bytes the batch reads
 };
+
+struct DecodeParams {
+  DecodeArgs a;
+  const DecodeUnit* units;
+  int64_t kv_bytes;       // K and V bytes the batch reads
+  InlinePlan<DecodeUnit> plan;  // plan.n > 0: the units
+};
+static_assert(sizeof(DecodeParams) <= 4096, "kernel arguments");
 
 struct DecodeMergeParams {
   const DecodeMerge* merges;
@@ -217,7 +251,9 @@ struct DecodeMergeParams {
   float* lse;
   int32_t num_q_heads;
   int32_t group;
+  InlineMerges<DecodeMerge> plan;  // plan.n > 0: the merges
 };
+static_assert(sizeof(DecodeMergeParams) <= 4096, "kernel arguments");
 
 hipError_t launch_decode(const DecodeParams& p, int64_t n_units, int head_dim, bool fp8, hipStream_t stream);
 hipError_t launch_decode_merge(const DecodeMergeParams& p, int64_t n_merges, int head_dim, hipStream_t stream);

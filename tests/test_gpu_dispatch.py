@@ -69,3 +69,19 @@ def test_decode_beyond_the_infinity_cache_gives_the_same_bits(dt, d):
             assert torch.equal(out.view(torch.int16), whole[r:r + 1].view(torch.int16)), r
     finally:
         run.close()
+
+
+@pytest.mark.parametrize("hq,hkv,prefix,extend,split", [
+    (8, 8, [700, 20], [90, 300], 0),       # eight heads side by side: one entry for eight units
+    (32, 16, [700, 20, 5], [9, 40, 33], 64),  # two heads per XCD, split parts
+    (8, 8, [8000], [200], 64),              # 126 parts a head: two launches write the plan
+    (8, 8, [15000, 9000], [40, 300], 64),   # beyond them: the plan is uploaded
+    (6, 3, [300, 77, 900], [200, 300, 64], 64),  # ungrouped units, one to three launches
+    (4, 2, [3000, 2500], [130, 100], 64),   # ungrouped, uploaded
+    (8, 8, [5000, 300, 64], [1, 1, 1], 64),  # decode: entries for eight units, merges in the arguments
+    (16, 8, [9000, 700], [1, 1], 64),       # decode: too many units, uploaded
+    (3, 3, [900, 31], [1, 1], 64),          # decode, ungrouped
+])
+def test_plans_in_kernel_arguments_and_uploaded(hq, hkv, prefix, extend, split):
+    w = wl.make_custom(prefix, extend, hq, hkv, 64, seed=64)
+    _run_and_compare(w, f"inline_{hkv}_{prefix[0]}_{extend[0]}", want_lse=True, fill=0x7FC0, split_keys=split)
