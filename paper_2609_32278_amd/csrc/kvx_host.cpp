@@ -266,6 +266,9 @@ struct Plan {
   std::vector<MergeUnit> merges;
   std::vector<kvx_work_item> items;  // same order, for inspection
   int64_t n_parts = 0;
+  std::vector<kvx::PlanTile> tiles;  // what the units are made of, and a code word each
+  std::vector<uint32_t> codes;       // (empty if the batch is beyond their limits)
+  int64_t split = 0;
   // decode units among the units (mixed batches)
   bool mixed = false;
   std::vector<kvx::DecodeMerge> dec_merges;
@@ -570,10 +573,17 @@ int make_plan(const kvx_batch* b, const std::vector<int64_t>& qo, int32_t Hq, in
   struct Placed {
     AttnUnit u;
     int32_t tok0;
+    uint32_t code;
   };
+  plan.tiles.clear();
+  plan.codes.clear();
+  plan.split = split;
+  const bool coded = !plan.mixed && tiles.size() < kvx::kPlanTiles - 1 && tiles.size() * 6 < (size_t)kvx::kPlanWords &&
+                     (uint32_t)Hkv <= kvx::kPlanHeads;
   std::vector<Placed> per_xcd[kvx::kNumXcd];
   plan.merges.clear();
   plan.n_parts = 0;
+  int64_t most_ranges = 0;
   for (size_t first = 0; first < tiles.size();) {  // one request at a time
     size_t last = first;
     while (last < tiles.size() && tiles[last].r == tiles[first].r) last++;
@@ -584,6 +594,10 @@ int make_plan(const kvx_batch* b, const std::vector<int64_t>& qo, int32_t Hq, in
       const Tile& t = tiles[k];
       const int64_t nb = boundaries(t);
       part0.push_back(plan.n_parts);
+      if (coded)
+        plan.tiles.push_back(kvx::PlanTile{(int32_t)(qo[(size_t)r] + t.tok0), (int32_t)t.qpos0, b->page_indptr[r],
+                                           (int32_t)t.kend, t.ntok << 16 | (int32_t)std::min<int64_t>(nb, 0xFFFF),
+                                           (int32_t)plan.n_parts});
       if (nb == 0) continue;
       for (int32_t h = 0; h < Hkv; h++)
         plan.merges.push_back(MergeUnit{(int32_t)(qo[(size_t)r] + t.tok0), (h << 16) | t.ntok,
@@ -591,6 +605,7 @@ int make_plan(const kvx_batch* b, const std::vector<int64_t>& qo, int32_t Hq, in
       plan.n_parts += (nb + 1) * Hkv;
     }
     const int64_t ranges = boundaries(tiles[first]) + 1;
+    most_ranges = std::max(most_ranges, ranges);
     for (int64_t i = 0; i < ranges; i++) {
       for (size_t k = first; k < last; k++) {
         const Tile& t = tiles[k];
@@ -609,7 +624,7 @@ int make_plan(const kvx_batch* b, const std::vector<int64_t>& qo, int32_t Hq, in
                                            (size_t)(run_of[k] * bind_parts[(size_t)r] + i)];
           u.head_ntok = (h << 16) | t.ntok;
           u.part = nb > 0 ? (int32_t)(part0[k - first] + h * (nb + 1) + i) : -1;
-          per_xcd[x].push_back(Placed{u, t.tok0});
+          per_xcd[x].push_back(Placed{u, t.tok0, kvx::plan_code((uint32_t)k, (uint32_t)h, (uint32_t)i)});
         }
       }
     }
@@ -624,7 +639,7 @@ int make_plan(const kvx_batch* b, const std::vector<int64_t>& qo, int32_t Hq, in
     for (int x = 0; x < kvx::kNumXcd; x++) {
       std::vector<Placed>& pre = per_xcd[x];
       std::vector<Placed> dec, all;
-      for (size_t i = (size_t)x; i < dec_units.size(); i += kvx::kNumXcd) dec.push_back(Placed{dec_units[i], 0});
+      for (size_t i = (size_t)x; i < dec_units.size(); i += kvx::kNumXcd) dec.push_back(Placed{dec_units[i], 0, 0});
       // An XCD's units go to its four shader engines strictly in turn (unit k to engine
       // k % 4, 8 CUs each) and in order, so that every engine must get both kinds alike:
       // they alternate in groups of four.
@@ -654,6 +669,7 @@ int make_plan(const kvx_batch* b, const std::vector<int64_t>& qo, int32_t Hq, in
       if (i < per_xcd[x].size()) {
         const AttnUnit& u = per_xcd[x][i].u;
         plan.units.push_back(u);
+        if (coded) plan.codes.push_back(per_xcd[x][i].code);
         const bool dec = (u.head_ntok & kvx::kDecodeUnitFlag) != 0;
         // inspected part numbers are dense: decode parts follow the prefill parts
         const int32_t part = dec && u.part >= 0 ? (int32_t)plan.n_parts + u.part : u.part;
@@ -663,6 +679,7 @@ int make_plan(const kvx_batch* b, const std::vector<int64_t>& qo, int32_t Hq, in
         AttnUnit pad{};
         pad.part = -1;
         plan.units.push_back(pad);
+        if (coded) plan.codes.push_back(kvx::kPlanPad);
         plan.items.push_back(kvx_work_item{-1, 0, 0, 0, 0, 0, -1, x});
       }
     }
@@ -671,7 +688,9 @@ int make_plan(const kvx_batch* b, const std::vector<int64_t>& qo, int32_t Hq, in
   while (!plan.units.empty() && plan.units.back().key_end <= plan.units.back().key_begin) {
     plan.units.pop_back();
     plan.items.pop_back();
+    if (coded) plan.codes.pop_back();
   }
+  if (most_ranges > (int64_t)kvx::kPlanRanges) plan.codes.clear();
   return KVX_OK;
 }
 
@@ -835,43 +854,54 @@ struct CallBuffers {
   }
 };
 
-void add_head(AttnUnit& u, int32_t h) { u.head_ntok += h << 16; }
-void add_head(DecodeUnit& u, int32_t h) { u.head += h; }
-
-// Units per entry of a small plan in kernel arguments (see InlinePlan): 8 if every group of
-// eight differs in its KV heads and parts alone, else 1; 0 for a plan of more than
-// `launches` argument blocks.
-template <typename U>
-int32_t inline_heads(const std::vector<U>& units, size_t launches) {
+// The units of a decode plan in kernel arguments, if they fit (see InlinePlan).
+bool inline_units(const std::vector<DecodeUnit>& units, kvx::InlinePlan<DecodeUnit>& out) {
   constexpr int32_t H = kvx::kNumXcd;
-  const size_t most = launches * kvx::kInlineUnits;
-  if (units.size() > most * H) return 0;
+  out.n = 0;
+  if (units.size() > (size_t)kvx::kInlineUnits * H) return false;
   bool grouped = units.size() % H == 0;
   for (size_t i = 0; grouped && i < units.size(); i += H) {
     const int32_t part = units[i].part, stride = part < 0 ? 0 : units[i + 1].part - part;
     for (int32_t h = 1; grouped && h < H; h++) {
-      U x = units[i];
-      add_head(x, h);
+      DecodeUnit x = units[i];
+      x.head += h;
       x.part = part < 0 ? -1 : part + h * stride;
-      grouped = std::memcmp(&x, &units[i + (size_t)h], sizeof(U)) == 0;
+      grouped = std::memcmp(&x, &units[i + (size_t)h], sizeof x) == 0;
     }
   }
-  return grouped ? H : units.size() <= most ? 1 : 0;
-}
-
-bool inline_units(const std::vector<DecodeUnit>& units, kvx::InlinePlan<DecodeUnit>& out) {
-  out.n = 0;
-  out.heads = inline_heads(units, 1);
-  if (out.heads == 0) return false;
+  if (!grouped && units.size() > (size_t)kvx::kInlineUnits) return false;
+  out.heads = grouped ? H : 1;
   for (size_t i = 0; i < units.size(); i += (size_t)out.heads) {
     DecodeUnit e = units[i];
-    e.req = out.heads > 1 && e.part >= 0 ? units[i + 1].part - e.part : 0;
+    e.req = grouped && e.part >= 0 ? units[i + 1].part - e.part : 0;
     out.unit[out.n++] = e;
   }
   return true;
 }
 
-// The same for its merges, which go tile by tile (request by request) with all KV heads.
+// A prefill plan in kernel arguments, if it fits (see CompactPlan).
+bool compact_plan(const Plan& plan, kvx::CompactPlan& out) {
+  constexpr int32_t H = kvx::kNumXcd;
+  const std::vector<uint32_t>& c = plan.codes;
+  const size_t room = (size_t)kvx::kPlanWords - std::min<size_t>(kvx::kPlanWords, 6 * plan.tiles.size());
+  if (c.empty() || c.size() > room * H) return false;
+  bool grouped = c.size() % H == 0;
+  for (size_t i = 0; grouped && i < c.size(); i++)
+    grouped = c[i] != kvx::kPlanPad && c[i] == c[i / H * H] + kvx::plan_code(0, (uint32_t)(i % H), 0);
+  if (!grouped && c.size() > room) return false;
+  out.n = (int32_t)c.size();
+  out.n_tiles = (int32_t)plan.tiles.size();
+  out.heads = grouped ? H : 1;
+  out.split = (int32_t)plan.split;
+  static_assert(sizeof(kvx::PlanTile) == 6 * sizeof(uint32_t), "six words per tile");
+  std::memcpy(out.words, plan.tiles.data(), plan.tiles.size() * sizeof(kvx::PlanTile));
+  uint32_t* w = out.words + 6 * plan.tiles.size();
+  for (size_t i = 0; i < c.size(); i += (size_t)out.heads) *w++ = c[i];
+  return true;
+}
+
+// The merges of either kind of plan in kernel arguments, if they fit; they go tile by tile
+// (request by request) with all KV heads.
 template <typename M>
 bool inline_merges(const std::vector<M>& merges, int32_t Hkv, kvx::InlineMerges<M>& out) {
   out.n = 0;
@@ -1422,6 +1452,7 @@ int kvx::attention_call(kvx_pool* pool, const kvx_batch* batch, const void* q, i
   Plan plan;
   kvx::AttnParams p;
   kvx::MergeParams m;
+  kvx::CompactPlan compact;
   bool in_args = false;
   std::vector<uint8_t> blob;  // one upload: units, then merges, then the decode units' merges
   for (const bool mixed : {true, false}) {
@@ -1431,10 +1462,7 @@ int kvx::attention_call(kvx_pool* pool, const kvx_batch* batch, const void* q, i
     plan = Plan();
     if (int rc = make_plan(batch, qo, num_q_heads, pool->num_kv_heads, D, pool->split_keys, lim, mixed, plan)) return rc;
     if (fixed && mixed && !plan.mixed) continue;  // no decode units: the whole region for the rest
-    // at most three launches that write the units: a copy through the staging buffer costs
-    // a small call about 15 us, a launch about 3
-    p.plan_heads = plan.mixed || !inline_merges(plan.merges, pool->num_kv_heads, m.plan) ? 0 : inline_heads(plan.units, 3);
-    in_args = p.plan_heads > 0;
+    in_args = inline_merges(plan.merges, pool->num_kv_heads, m.plan) && compact_plan(plan, compact);
     if (in_args) break;
     m.plan.n = 0;
     blob = plan_blob(plan.units, plan.merges, plan.dec_merges);
@@ -1452,8 +1480,7 @@ int kvx::attention_call(kvx_pool* pool, const kvx_batch* batch, const void* q, i
       return rc;
   void* dev = nullptr;
   if (int rc = in_args ? buf.reserve(plan.units.size() * sizeof(AttnUnit), s, &dev) : buf.upload(blob, s, &dev)) return rc;
-  p.host_units = plan.units.data();
-  p.plan_units = in_args ? (int32_t)plan.units.size() : 0;
+  p.compact = in_args ? &compact : nullptr;
 
   p.q = (const uint16_t*)q;
   p.out = (uint16_t*)out;

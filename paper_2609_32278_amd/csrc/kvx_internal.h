@@ -50,10 +50,12 @@ struct StoreUnit {
 };
 
 // Small plans travel in kernel arguments instead of through a copy (whose start and end
-// cost a small call more than its kernels).  An entry stands for `heads` units: unit i
-// is entry i / heads, with i % heads added to its KV head and (i % heads) times a stride
-// (kept in `req`, which no kernel uses) to its part.  heads is 8 where groups of eight units
-// differ in nothing else (eight KV heads side by side on the eight XCDs), else 1.
+// cost a small call more than its kernels).
+//
+// Decode: entry e of the arguments stands for `heads` units, unit i being entry i / heads
+// with i % heads added to its KV head and (i % heads) times a stride (kept in `req`, which
+// no kernel uses) to its part.  heads is 8 where groups of eight units differ in nothing else
+// (eight KV heads side by side on the eight XCDs), else 1.
 constexpr int kInlineUnits = 110;   // 32-byte units: the arguments stay below 4 KiB
 constexpr int kInlineMerges = 220;  // 16-byte merges, one entry for all KV heads of a tile
 template <typename U>
@@ -61,6 +63,28 @@ struct InlinePlan {
   int32_t n;      // entries; 0: the units are uploaded
   int32_t heads;  // units per entry
   U unit[kInlineUnits];
+};
+// Prefill: a kernel writes the units to the plan buffer from the tiles they belong to and a
+// code word per unit, or per `heads` units as above (the attention kernels read their units
+// from memory only: their main loop has no scalar register to spare for choosing between
+// two places).
+struct PlanTile {
+  int32_t qo_row0, q_pos0, page_base;
+  int32_t kend;    // keys [0, kend)
+  int32_t ntok_nb;  // (tokens << 16) | split boundaries below kend (parts - 1)
+  int32_t part0;   // part of (KV head 0, range 0); head h is h * parts further on
+};
+constexpr int kPlanWords = 960;  // tiles (6 words each), then code words
+constexpr uint32_t kPlanPad = 0xFFFFFFFFu;
+inline uint32_t plan_code(uint32_t tile, uint32_t head, uint32_t range) { return tile << 20 | head << 10 | range; }
+constexpr uint32_t kPlanTiles = 1 << 12, kPlanHeads = 1 << 10, kPlanRanges = 1 << 10;  // limits of the code (tile
+                                                                                       // kPlanTiles - 1 is kPlanPad's)
+struct CompactPlan {
+  int32_t n;        // units
+  int32_t n_tiles;
+  int32_t heads;    // units per code word
+  int32_t split;    // keys per range
+  uint32_t words[kPlanWords];
 };
 template <typename M>
 struct InlineMerges {
@@ -89,12 +113,9 @@ struct AttnParams {
   int32_t mixed;          // 1: the plan holds decode units too
   float* d_part;          // fp32 [decode parts, kDecodeMaxGroup, D]
   float* d_lse;           // fp32 [decode parts, kDecodeMaxGroup]
-  // For the launcher: plan_units > 0 units in host memory, which it writes to `units` by a
-  // kernel of its own (the attention kernels read their units from there only: their main
-  // loop has no scalar register to spare for choosing between two places).
-  const AttnUnit* host_units;
-  int32_t plan_heads;  // as InlinePlan::heads
-  int32_t plan_units;
+  // For the launcher: a plan (in host memory) that it writes to `units` by a kernel, or null
+  // when the units were uploaded.
+  const CompactPlan* compact;
 };
 
 struct MergeParams {
