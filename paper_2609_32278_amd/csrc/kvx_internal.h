@@ -193,8 +193,11 @@ struct RopeParams {
   StoreReqs reqs;                   // reqs.n > 0: the units come from here instead
 };
 
+// Page ids of one launch of the page I/O kernel in its arguments.
+constexpr int kInlinePages = 960;
 struct PageIoParams {
-  const int32_t* page_ids;  // device [n]
+  const int32_t* page_ids;  // device [n], or null: host_ids
+  const int32_t* host_ids;  // for the launcher: host [n], carried in kernel arguments
   void* k_pool;
   void* v_pool;
   void* k_lin;              // canonical [n][Hkv][16][D] buffers

@@ -124,3 +124,25 @@ def test_store_leaves_prefix_slots_of_a_shared_page_alone():
             assert np.array_equal(after_v[page_row, :, : p % 16], before_v[page_row, :, : p % 16])
     finally:
         run.close()
+
+
+@pytest.mark.parametrize("n", [1, 959, 960, 961, 1921, 7680, 7681])
+def test_page_io_counts_around_the_argument_blocks(n):
+    """Page ids travel in kernel arguments, 960 to a launch, up to 7680; more are uploaded.
+    Every page must come back from where it was written."""
+    print(f"[store] page io n={n}", flush=True)
+    pool = kvx.kv_pool_create(n + 3, 16, 1, 64, kvx.KVX_KV_FP8_E4M3, np.ones(1, np.float32), np.ones(1, np.float32))
+    try:
+        g = torch.Generator(device=DEV).manual_seed(n)
+        k = torch.randint(0, 127, (n, 1, 16, 64), generator=g, device=DEV, dtype=torch.uint8)
+        v = torch.randint(0, 127, (n, 1, 16, 64), generator=g, device=DEV, dtype=torch.uint8)
+        ids = np.random.default_rng(n).permutation(n + 3)[:n].astype(np.int32)
+        kvx.kv_pool_write_pages(pool, ids, k, v)
+        back = np.argsort(ids)  # read in page order: other ids per launch than at the write
+        k2, v2 = torch.zeros_like(k), torch.zeros_like(v)
+        kvx.kv_pool_read_pages(pool, ids[back], k2, v2)
+        torch.cuda.synchronize()
+        order = torch.from_numpy(back.copy()).to(DEV)
+        assert torch.equal(k2, k[order]) and torch.equal(v2, v[order])
+    finally:
+        kvx.kv_pool_destroy(pool)
