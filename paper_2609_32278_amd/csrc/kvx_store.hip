@@ -9,7 +9,10 @@
 // One workgroup handles one page of one request for one group of 4 KV heads
 // (head_dim 128) or 8 (head_dim 64) -- grid x = the page, y = the head group, so
 // that a batch touching few pages still fills the chip -- and issues all of its
-// loads before using any (four K and four V 16-byte loads in flight per thread):
+// loads before using any (four K and four V 16-byte loads in flight per thread; its
+// 16-byte stores, like the fused store's, are non-temporal: 48k tokens of 8/1/128 heads
+// 58 -> 46 us, 27k tokens of 64/8/128 heads 221 -> 216 us, 16k tokens of 8 K/V heads 24.6
+// -> 21.0 us, and no turn whose attention reads them back got slower):
 // K rows are copied with 16-byte accesses, V rows are staged in LDS and written
 // out transposed, one 16-slot column (32 bytes bf16 / 16 bytes fp8) per dim.
 // fp8 pool: code = e4m3_rne(clamp(x * inv_scale_h, -448, 448)) with the
@@ -88,7 +91,7 @@ __device__ __forceinline__ void write_vt(const uint16_t (&vs)[kPageSize][D + 8],
         w.y = raw[2] | ((uint32_t)raw[3] << 16);
         w.z = raw[4] | ((uint32_t)raw[5] << 16);
         w.w = raw[6] | ((uint32_t)raw[7] << 16);
-        *(uint4*)dst = w;
+        store16<true>(dst, w);
       } else {
         for (int e = 0; e < 8; e++)
           if (s0 + e >= slot_begin && s0 + e < slot_end) dst[e] = raw[e];
@@ -167,7 +170,7 @@ __global__ __launch_bounds__(kStoreThreads) void store_kv_kernel(StoreParams p) 
                           bf16_to_f32(ke[6]) * kinv, bf16_to_f32(ke[7]) * kinv);
           *(uint2*)((uint8_t*)p.k_pool + blk + (size_t)slot * D + cc * 8) = code;
         } else {
-          *(uint4*)((uint16_t*)p.k_pool + blk + (size_t)slot * D + cc * 8) = kx[j];
+          store16<true>((uint16_t*)p.k_pool + blk + (size_t)slot * D + cc * 8, kx[j]);
         }
       }
       *(uint4*)(&vs[hb][slot][cc * 8]) = vx[j];
@@ -378,7 +381,7 @@ __global__ __launch_bounds__(kStoreThreads) void store_kv_rope_kernel(RopeParams
     uint16_t* qo = p.q_out + (size_t)row0 * Hq * D;
     rope_rows<D, INTERLEAVED>(p.q + (size_t)row0 * Hq * D, ntok, Hq, h0, nh, p.lg_q, u.slot_begin, sm.cs, p.q_norm,
                               p.norm_eps, p.rotary_dim, angles, [&](int tok, int hd, int cc, const float(&v)[8]) {
-                                *(uint4*)(qo + ((size_t)tok * Hq + hd) * D + cc * 8) = pack_bf16x8(v);
+                                store16<true>(qo + ((size_t)tok * Hq + hd) * D + cc * 8, pack_bf16x8(v));
                               });
     if (!whole) return;
   }
@@ -397,7 +400,7 @@ __global__ __launch_bounds__(kStoreThreads) void store_kv_rope_kernel(RopeParams
             code.y = e4m3x4(v[4] * kinv, v[5] * kinv, v[6] * kinv, v[7] * kinv);
             *(uint2*)((uint8_t*)p.k_pool + blk + (size_t)slot * D + cc * 8) = code;
           } else {
-            *(uint4*)((uint16_t*)p.k_pool + blk + (size_t)slot * D + cc * 8) = pack_bf16x8(v);
+            store16<true>((uint16_t*)p.k_pool + blk + (size_t)slot * D + cc * 8, pack_bf16x8(v));
           }
         });
     if (!whole) return;
