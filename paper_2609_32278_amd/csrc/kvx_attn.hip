@@ -70,43 +70,12 @@ __global__ __launch_bounds__(256) void merge_kernel(MergeParams p) {
 
 }  // namespace
 
-struct WritePlanParams {
-  AttnUnit* out;
-  CompactPlan plan;
-};
-static_assert(sizeof(WritePlanParams) <= 4096, "kernel arguments");
-
-// Write the units of a compact plan to the plan buffer.
-__global__ __launch_bounds__(256) void write_plan_kernel(WritePlanParams p) {
-  const int i = blockIdx.x * 256 + threadIdx.x;
-  if (i >= p.plan.n) return;
-  const uint32_t code = p.plan.words[6 * p.plan.n_tiles + i / p.plan.heads];
-  AttnUnit u{};
-  u.part = -1;
-  if (code != kPlanPad) {
-    const uint32_t* t = p.plan.words + 6 * (code >> 20);
-    const int h = (int)(code >> 10 & (kPlanHeads - 1)) + i % p.plan.heads, range = (int)(code & (kPlanRanges - 1));
-    const int ntok = (int)t[4] >> 16, nb = (int)t[4] & 0xFFFF;
-    u.qo_row0 = (int)t[0];
-    u.q_pos0 = (int)t[1];
-    u.page_base = (int)t[2];
-    u.key_begin = range * p.plan.split;
-    u.key_end = range < nb ? (range + 1) * p.plan.split : (int)t[3];
-    u.head_ntok = h << 16 | ntok;
-    if (nb > 0) u.part = (int)t[5] + h * (nb + 1) + range;
-  }
-  p.out[i] = u;
-}
-
 hipError_t launch_extend_attention(const AttnParams& p, int64_t n_units, int head_dim, bool fp8, bool scaled_q,
                                    hipStream_t stream) {
   if (n_units <= 0) return hipSuccess;
-  if (p.compact != nullptr) {
-    const WritePlanParams w{const_cast<AttnUnit*>(p.units), *p.compact};
-    hipLaunchKernelGGL(write_plan_kernel, dim3((unsigned)((w.plan.n + 255) / 256)), dim3(256), 0, stream, w);
-  }
+  if (p.compact != nullptr) return launch_small_attention(p, n_units, head_dim, fp8, scaled_q, stream);
   if (p.mixed) return launch_mixed_attention(p, n_units, head_dim, fp8, scaled_q, stream);
-  launch_attn<false>(p, n_units, head_dim, fp8, scaled_q, stream);
+  launch_attn<false>(p, UnitsInMemory{}, n_units, head_dim, fp8, scaled_q, stream);
   return hipGetLastError();
 }
 

@@ -51,6 +51,8 @@
 
 #pragma once
 
+#include <type_traits>
+
 #include "kvx_decode_unit.h"
 #include "kvx_internal.h"
 
@@ -408,6 +410,27 @@ __device__ __forceinline__ void folded_rescale(f32x16 (&st)[kKB], f32x16 (&o)[Ge
   }
 }
 
+// Unit i of a compact plan whose words are at `words`.
+template <class Words>
+__device__ __forceinline__ AttnUnit unit_from_plan(const CompactPlan& plan, Words words, int i) {
+  const uint32_t code = (uint32_t)words[6 * plan.n_tiles + i / plan.heads];
+  AttnUnit u{};
+  u.part = -1;
+  if (code != kPlanPad) {
+    const Words t = words + 6 * (code >> 20);
+    const int h = (int)(code >> 10 & (kPlanHeads - 1)) + i % plan.heads, range = (int)(code & (kPlanRanges - 1));
+    const int ntok = (int)t[4] >> 16, nb = (int)t[4] & 0xFFFF;
+    u.qo_row0 = (int)t[0];
+    u.q_pos0 = (int)t[1];
+    u.page_base = (int)t[2];
+    u.key_begin = range * plan.split;
+    u.key_end = range < nb ? (range + 1) * plan.split : (int)t[3];
+    u.head_ntok = h << 16 | ntok;
+    if (nb > 0) u.part = (int)t[5] + h * (nb + 1) + range;
+  }
+  return u;
+}
+
 // The work item of this workgroup (scalar loads: every index derived from it stays
 // uniform) and the lane's query row within it.
 struct Rows {
@@ -421,17 +444,29 @@ struct Rows {
   bool valid;   // the row is a real query (its token exists)
 };
 
-__device__ __forceinline__ Rows rows_of(const AttnParams& p) {
+// Where the units are: in memory (AttnParams::units), or written out from the compact plan
+// in the kernel's arguments, which follow AttnParams there.
+struct UnitsInMemory {};
+
+template <class Plan>
+__device__ __forceinline__ Rows rows_of(const AttnParams& p, const Plan& plan) {
   Rows r;
-  const const_i32_ptr w = (const_i32_ptr)(p.units + blockIdx.x);
-  r.u.qo_row0 = w[0];
-  r.u.q_pos0 = w[1];
-  r.u.page_base = w[2];
-  r.u.key_begin = w[3];
-  r.u.key_end = w[4];
-  r.u.head_ntok = w[5];
-  r.u.part = w[6];
-  r.u.req = w[7];
+  if constexpr (std::is_same_v<Plan, CompactPlan>) {
+    const const_i32_ptr words =
+        (const_i32_ptr)((const __attribute__((address_space(4))) char*)__builtin_amdgcn_kernarg_segment_ptr() +
+                        sizeof(AttnParams) + offsetof(CompactPlan, words));
+    r.u = unit_from_plan(plan, words, blockIdx.x);
+  } else {
+    const const_i32_ptr w = (const_i32_ptr)(p.units + blockIdx.x);
+    r.u.qo_row0 = w[0];
+    r.u.q_pos0 = w[1];
+    r.u.page_base = w[2];
+    r.u.key_begin = w[3];
+    r.u.key_end = w[4];
+    r.u.head_ntok = w[5];
+    r.u.part = w[6];
+    r.u.req = w[7];
+  }
   r.lane = threadIdx.x & 63;
   r.wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   r.n = r.lane & 31;
@@ -574,8 +609,8 @@ __device__ __forceinline__ bool run_decode_unit(const AttnParams& p, uint8_t* o_
 // ---------------------------------------------------------------- bf16 pool
 
 // SQ: folded softmax (Q scaled and rounded once more to bf16, see the file header).
-template <int D, bool SQ, bool MIXED>
-__global__ __launch_bounds__(kAttnThreads, 1) void extend_attn_kernel(AttnParams p) {
+template <int D, bool SQ, bool MIXED, class Plan>
+__global__ __launch_bounds__(kAttnThreads, 1) void extend_attn_kernel(AttnParams p, Plan plan) {
   using G = Geom<D>;
   __shared__ __attribute__((aligned(1024))) uint8_t k_lds[G::NSTAGE][G::TILE_BYTES];
   __shared__ __attribute__((aligned(1024))) uint8_t v_lds[G::NSTAGE][G::TILE_BYTES];
@@ -584,7 +619,7 @@ __global__ __launch_bounds__(kAttnThreads, 1) void extend_attn_kernel(AttnParams
     if (run_decode_unit<D, false>(p, k_lds[0], v_lds[0])) return;
   }
 
-  const Rows r = rows_of(p);
+  const Rows r = rows_of(p, plan);
   const AttnUnit& u = r.u;
   if (u.key_end <= u.key_begin) return;  // padding entry: uniform exit
   const int lane = r.lane, wave = r.wave, h = r.h, qpos = r.qpos;
@@ -937,8 +972,8 @@ __device__ __forceinline__ uint4 zero_past(uint4 x, int key, int key_end) {
   return x;
 }
 
-template <int D, bool MIXED>
-__global__ __launch_bounds__(kAttnThreads, 1) void extend_attn_fp8_kernel(AttnParams p) {
+template <int D, bool MIXED, class Plan>
+__global__ __launch_bounds__(kAttnThreads, 1) void extend_attn_fp8_kernel(AttnParams p, Plan plan) {
   using G = Geom<D>;
   using G8 = Geom8<D>;
   // one block, bf16 buffers first: every MFMA operand read and conversion write then
@@ -953,7 +988,7 @@ __global__ __launch_bounds__(kAttnThreads, 1) void extend_attn_fp8_kernel(AttnPa
     if (run_decode_unit<D, true>(p, lds, lds + O_BYTES)) return;
   }
 
-  const Rows r = rows_of(p);
+  const Rows r = rows_of(p, plan);
   const AttnUnit& u = r.u;
   if (u.key_end <= u.key_begin) return;  // padding entry: uniform exit
   const int lane = r.lane, wave = r.wave, h = r.h, qpos = r.qpos;
@@ -1182,17 +1217,18 @@ __global__ __launch_bounds__(kAttnThreads, 1) void extend_attn_fp8_kernel(AttnPa
   write_result<D>(p, r, o, l_run, m_run, vscale);
 }
 
-template <bool MIXED>
-void launch_attn(const AttnParams& p, int64_t n_units, int head_dim, bool fp8, bool scaled_q, hipStream_t stream) {
+template <bool MIXED, class Plan>
+void launch_attn(const AttnParams& p, const Plan& plan, int64_t n_units, int head_dim, bool fp8, bool scaled_q,
+                 hipStream_t stream) {
   const dim3 grid((unsigned)n_units), block(kAttnThreads);
   if (head_dim == 128) {
-    if (fp8) hipLaunchKernelGGL((extend_attn_fp8_kernel<128, MIXED>), grid, block, 0, stream, p);
-    else if (scaled_q) hipLaunchKernelGGL((extend_attn_kernel<128, true, MIXED>), grid, block, 0, stream, p);
-    else hipLaunchKernelGGL((extend_attn_kernel<128, false, MIXED>), grid, block, 0, stream, p);
+    if (fp8) hipLaunchKernelGGL((extend_attn_fp8_kernel<128, MIXED, Plan>), grid, block, 0, stream, p, plan);
+    else if (scaled_q) hipLaunchKernelGGL((extend_attn_kernel<128, true, MIXED, Plan>), grid, block, 0, stream, p, plan);
+    else hipLaunchKernelGGL((extend_attn_kernel<128, false, MIXED, Plan>), grid, block, 0, stream, p, plan);
   } else {
-    if (fp8) hipLaunchKernelGGL((extend_attn_fp8_kernel<64, MIXED>), grid, block, 0, stream, p);
-    else if (scaled_q) hipLaunchKernelGGL((extend_attn_kernel<64, true, MIXED>), grid, block, 0, stream, p);
-    else hipLaunchKernelGGL((extend_attn_kernel<64, false, MIXED>), grid, block, 0, stream, p);
+    if (fp8) hipLaunchKernelGGL((extend_attn_fp8_kernel<64, MIXED, Plan>), grid, block, 0, stream, p, plan);
+    else if (scaled_q) hipLaunchKernelGGL((extend_attn_kernel<64, true, MIXED, Plan>), grid, block, 0, stream, p, plan);
+    else hipLaunchKernelGGL((extend_attn_kernel<64, false, MIXED, Plan>), grid, block, 0, stream, p, plan);
   }
 }
 

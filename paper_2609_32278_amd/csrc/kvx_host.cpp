@@ -97,6 +97,7 @@ struct Staging {
   // The caller records done() on the stream after the kernels that read it.
   int upload(const void* src, size_t bytes, hipStream_t stream, void** out) {
     if (!ev) KVX_HIP(hipEventCreateWithFlags(&ev, hipEventDisableTiming));
+    if (!used) KVX_HIP(hipEventCreateWithFlags(&used, hipEventDisableTiming));
     if (pending) {
       KVX_HIP(hipEventSynchronize(ev));
       pending = false;
@@ -108,17 +109,6 @@ struct Staging {
       KVX_HIP(hipHostMalloc(&host, cap, hipHostMallocDefault));
       host_cap = cap;
     }
-    if (int rc = reserve(bytes, stream, out)) return rc;
-    std::memcpy(host, src, bytes);
-    KVX_HIP(hipMemcpyAsync(dev, host, bytes, hipMemcpyHostToDevice, stream));
-    KVX_HIP(hipEventRecord(ev, stream));
-    pending = true;
-    return KVX_OK;
-  }
-
-  // Device memory of at least `bytes`, for a kernel on `stream` to fill (as upload's).
-  int reserve(size_t bytes, hipStream_t stream, void** out) {
-    if (!used) KVX_HIP(hipEventCreateWithFlags(&used, hipEventDisableTiming));
     if (bytes > dev_cap) {
       if (dev) {
         // earlier kernels (on any stream) that read the old buffer precede `used`
@@ -131,6 +121,10 @@ struct Staging {
       KVX_HIP(hipMallocAsync(&dev, cap, stream));
       dev_cap = cap;
     }
+    std::memcpy(host, src, bytes);
+    KVX_HIP(hipMemcpyAsync(dev, host, bytes, hipMemcpyHostToDevice, stream));
+    KVX_HIP(hipEventRecord(ev, stream));
+    pending = true;
     *out = dev;
     return KVX_OK;
   }
@@ -828,14 +822,6 @@ struct CallBuffers {
     *out = (float*)pool->parts.ptr;
     return KVX_OK;
   }
-  // Room for a plan that a kernel writes.
-  int reserve(size_t bytes, hipStream_t s, void** out) {
-    if (fixed) {
-      *out = base;
-      return KVX_OK;
-    }
-    return pool->st_attn.reserve(bytes, s, out);
-  }
   int upload(const std::vector<uint8_t>& blob, hipStream_t s, void** out) {
     if (fixed) {
       // pageable source: the copy is staged before the call returns
@@ -1468,13 +1454,16 @@ int kvx::attention_call(kvx_pool* pool, const kvx_batch* batch, const void* q, i
     if (int rc = make_plan(batch, qo, num_q_heads, pool->num_kv_heads, D, pool->split_keys, lim, mixed, plan)) return rc;
     if (fixed && mixed && !plan.mixed) continue;  // no decode units: the whole region for the rest
     in_args = inline_merges(plan.merges, pool->num_kv_heads, m.plan) && compact_plan(plan, compact);
-    if (in_args) break;
+    if (in_args) {
+      blob.clear();
+      break;
+    }
     m.plan.n = 0;
     blob = plan_blob(plan.units, plan.merges, plan.dec_merges);
     // a mixed plan has more units: what does not fit its region may fit without it
     if (!(plan.mixed && fixed && blob.size() > fixed->plan_bytes)) break;
   }
-  if (int rc = buf.check_plan(in_args ? plan.units.size() * sizeof(AttnUnit) : blob.size())) return rc;
+  if (int rc = buf.check_plan(blob.size())) return rc;
   if (int rc = use_device(pool)) return rc;
   if (validate_mode())
     if (int rc = check_page_ids(pool, batch, s)) return rc;
@@ -1484,7 +1473,8 @@ int kvx::attention_call(kvx_pool* pool, const kvx_batch* batch, const void* q, i
     if (int rc = buf.parts((size_t)plan.n_parts * part_bytes + (size_t)plan.dec_parts * dec_part_bytes, s, &parts))
       return rc;
   void* dev = nullptr;
-  if (int rc = in_args ? buf.reserve(plan.units.size() * sizeof(AttnUnit), s, &dev) : buf.upload(blob, s, &dev)) return rc;
+  if (!in_args)
+    if (int rc = buf.upload(blob, s, &dev)) return rc;
   p.compact = in_args ? &compact : nullptr;
 
   p.q = (const uint16_t*)q;
@@ -1534,5 +1524,5 @@ int kvx::attention_call(kvx_pool* pool, const kvx_batch* batch, const void* q, i
     e = kvx::launch_decode_merge(dm, (int64_t)plan.dec_merges.size(), D, s);
     if (e != hipSuccess) return hip_fail(e, "decode merge kernel launch");
   }
-  return buf.done(s, true);
+  return buf.done(s, !in_args);
 }

@@ -64,10 +64,8 @@ struct InlinePlan {
   int32_t heads;  // units per entry
   U unit[kInlineUnits];
 };
-// Prefill: a kernel writes the units to the plan buffer from the tiles they belong to and a
-// code word per unit, or per `heads` units as above (the attention kernels read their units
-// from memory only: their main loop has no scalar register to spare for choosing between
-// two places).
+// Prefill: the tiles the units belong to, and a code word per unit, or per `heads` units as
+// above.  The kernels that take them are instantiations of their own (kvx_small.hip).
 struct PlanTile {
   int32_t qo_row0, q_pos0, page_base;
   int32_t kend;    // keys [0, kend)
@@ -113,8 +111,8 @@ struct AttnParams {
   int32_t mixed;          // 1: the plan holds decode units too
   float* d_part;          // fp32 [decode parts, kDecodeMaxGroup, D]
   float* d_lse;           // fp32 [decode parts, kDecodeMaxGroup]
-  // For the launcher: a plan (in host memory) that it writes to `units` by a kernel, or null
-  // when the units were uploaded.
+  // For the launcher: the plan (in host memory) for the kernel arguments, or null when the
+  // units were uploaded.
   const CompactPlan* compact;
 };
 
@@ -306,6 +304,9 @@ hipError_t launch_extend_attention(const AttnParams& p, int64_t n_units, int hea
                                    hipStream_t stream);
 // launch_extend_attention of a plan that holds decode units (p.mixed)
 hipError_t launch_mixed_attention(const AttnParams& p, int64_t n_units, int head_dim, bool fp8, bool scaled_q,
+                                  hipStream_t stream);
+// ... and of a compact plan, from the kernel arguments
+hipError_t launch_small_attention(const AttnParams& p, int64_t n_units, int head_dim, bool fp8, bool scaled_q,
                                   hipStream_t stream);
 hipError_t launch_merge(const MergeParams& p, int64_t n_merges, int head_dim, hipStream_t stream);
 hipError_t launch_store_kv(const StoreParams& p, int64_t n_units, int head_dim, bool fp8,

@@ -9,7 +9,7 @@ namespace kvx {
 
 hipError_t launch_mixed_attention(const AttnParams& p, int64_t n_units, int head_dim, bool fp8, bool scaled_q,
                                   hipStream_t stream) {
-  launch_attn<true>(p, n_units, head_dim, fp8, scaled_q, stream);
+  launch_attn<true>(p, UnitsInMemory{}, n_units, head_dim, fp8, scaled_q, stream);
   return hipGetLastError();
 }
 
