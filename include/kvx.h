@@ -26,10 +26,11 @@
  *     pool that overlap on two streams race on those buffers, and calls on one
  *     pool must come from one host thread at a time.  Separate pools are
  *     independent.
- *   - Calls build their work plan on the host and upload it through a pinned
- *     staging buffer, waiting on the host for that buffer's previous copy, and
- *     may allocate device scratch the first time a size is seen: they are not
- *     meant to be captured into a HIP graph.  Scratch grows with the
+ *   - Calls build their work plan on the host.  A small plan travels in the
+ *     kernel arguments; a larger one is uploaded through a pinned staging buffer,
+ *     waiting on the host for that buffer's previous copy.  Calls may allocate
+ *     device scratch the first time a size is seen: they are not meant to be
+ *     captured into a HIP graph.  Scratch grows with the
  *     stream-ordered allocator (hipMallocAsync / hipFreeAsync): growing never
  *     waits for the device on the host.
  *   - "host" pointers are ordinary CPU memory read during the call;
@@ -255,15 +256,15 @@ int extend_attention(kvx_pool *pool, const kvx_batch *batch, const void *q, int3
 /*
  * extend_attention for callers that cannot allocate device memory during the
  * call: tight serving loops and harnesses that forbid hipMalloc.  It is still
- * not capturable into a HIP graph: each call builds its plan on the host and
- * copies it from a host vector that is freed when the call returns, so a
- * captured copy would read freed memory on replay.  Same arguments, operation, kernels and result as extend_attention
+ * not capturable into a HIP graph: each call builds its plan on the host and,
+ * unless it fits the kernel arguments, copies it from a host vector that is freed
+ * when the call returns, so a captured copy would read freed memory on replay.  Same arguments, operation, kernels and result as extend_attention
  * (bit for bit when both split the key ranges alike), but the work plan and the
  * partial results of split key ranges go into one fixed device array of the
  * library instead of the pool's staging buffer and workspace; the call makes no
- * device or pinned allocation (only host containers for the plan).  The plan is
- * copied from pageable host memory (hipMemcpyAsync, staged before the call
- * returns).
+ * device or pinned allocation (only host containers for the plan).  A plan beyond
+ * the kernel arguments is copied from pageable host memory (hipMemcpyAsync, staged
+ * before the call returns).
  *   The array holds KVX_NOALLOC_PLAN_BYTES of plan (32 B per work item) and
  *   KVX_NOALLOC_PARTS_BYTES of partial results; the planner splits key ranges
  *   only into as many parts as fit.  A batch whose plan does not fit is refused

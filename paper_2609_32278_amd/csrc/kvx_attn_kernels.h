@@ -410,27 +410,6 @@ __device__ __forceinline__ void folded_rescale(f32x16 (&st)[kKB], f32x16 (&o)[Ge
   }
 }
 
-// Unit i of a compact plan whose words are at `words`.
-template <class Words>
-__device__ __forceinline__ AttnUnit unit_from_plan(const CompactPlan& plan, Words words, int i) {
-  const uint32_t code = (uint32_t)words[6 * plan.n_tiles + i / plan.heads];
-  AttnUnit u{};
-  u.part = -1;
-  if (code != kPlanPad) {
-    const Words t = words + 6 * (code >> 20);
-    const int h = (int)(code >> 10 & (kPlanHeads - 1)) + i % plan.heads, range = (int)(code & (kPlanRanges - 1));
-    const int ntok = (int)t[4] >> 16, nb = (int)t[4] & 0xFFFF;
-    u.qo_row0 = (int)t[0];
-    u.q_pos0 = (int)t[1];
-    u.page_base = (int)t[2];
-    u.key_begin = range * plan.split;
-    u.key_end = range < nb ? (range + 1) * plan.split : (int)t[3];
-    u.head_ntok = h << 16 | ntok;
-    if (nb > 0) u.part = (int)t[5] + h * (nb + 1) + range;
-  }
-  return u;
-}
-
 // The work item of this workgroup (scalar loads: every index derived from it stays
 // uniform) and the lane's query row within it.
 struct Rows {

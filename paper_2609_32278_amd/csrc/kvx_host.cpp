@@ -2,7 +2,8 @@
 //
 // Owns the KV pool (hipMalloc), checks every argument before queuing work,
 // plans extend_attention's work over ragged (prefix_len, extend_len) pairs and
-// uploads the plan through pinned staging buffers on the caller's stream.
+// passes the plan in kernel arguments where it is small, else uploads it through
+// pinned staging buffers on the caller's stream.
 
 #include <algorithm>
 #include <cmath>

@@ -91,6 +91,27 @@ struct InlineMerges {
   M merge[kInlineMerges];
 };
 
+// Unit i of a compact plan whose words are at `words` (constexpr: for the host and the device).
+template <class Words>
+constexpr AttnUnit unit_from_plan(const CompactPlan& plan, Words words, int i) {
+  const uint32_t code = (uint32_t)words[6 * plan.n_tiles + i / plan.heads];
+  AttnUnit u{};
+  u.part = -1;
+  if (code != kPlanPad) {
+    const Words t = words + 6 * (code >> 20);
+    const int h = (int)(code >> 10 & (kPlanHeads - 1)) + i % plan.heads, range = (int)(code & (kPlanRanges - 1));
+    const int ntok = (int)t[4] >> 16, nb = (int)t[4] & 0xFFFF;
+    u.qo_row0 = (int)t[0];
+    u.q_pos0 = (int)t[1];
+    u.page_base = (int)t[2];
+    u.key_begin = range * plan.split;
+    u.key_end = range < nb ? (range + 1) * plan.split : (int)t[3];
+    u.head_ntok = h << 16 | ntok;
+    if (nb > 0) u.part = (int)t[5] + h * (nb + 1) + range;
+  }
+  return u;
+}
+
 struct AttnParams {
   const uint16_t* q;      // bf16 [T, Hq, D]
   uint16_t* out;          // bf16 [T, Hq, D]
@@ -293,9 +314,9 @@ struct FixedScratch {
 };
 
 // extend_attention's whole call: argument checks, plan, upload, launches.  With
-// fixed == nullptr the plan goes through the pool's staging buffer and split
-// parts into its growable workspace; otherwise both go into the fixed scratch,
-// the plan is bounded by its regions (EUNSUPPORTED beyond them, checked on the
+// fixed == nullptr a plan too large for the kernel arguments goes through the pool's
+// staging buffer and split parts into its growable workspace; otherwise both go into
+// the fixed scratch, the plan is bounded by its regions (EUNSUPPORTED beyond them, checked on the
 // host before any device call) and nothing is allocated.
 int attention_call(kvx_pool* pool, const kvx_batch* batch, const void* q, int32_t num_q_heads, float sm_scale,
                    void* out, float* lse, kvx_stream_t stream, const FixedScratch* fixed);

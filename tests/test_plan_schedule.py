@@ -3,6 +3,8 @@ dispatch -- 32 workgroup slots per XCD taking its units in plan order -- ends cl
 perfect balance, for batches the planner splits and for batches it does not."""
 
 import heapq
+import os
+import shutil
 
 import numpy as np
 import pytest
@@ -10,6 +12,7 @@ import pytest
 from paper_2609_32278_amd import kvx
 from paper_2609_32278_amd import workloads as wl
 from test_abi import _check_plan
+from test_sanitizers import ROOT, SAN, _build_and_run
 
 
 def _replay(items):
@@ -49,3 +52,14 @@ def test_short_batches_are_split_until_the_start_of_a_unit_dominates():
     assert len(real) > 100
     inner = real[real["key_end"] < real["key_end"].max() - 700]
     assert (inner["key_end"] - inner["key_begin"] >= 256).all()
+
+
+@pytest.mark.skipif(shutil.which("g++") is None or not os.path.exists("/opt/rocm/lib/libamdhip64.so"),
+                    reason="g++ or the HIP runtime library not installed")
+def test_plans_in_kernel_arguments_expand_to_the_uploaded_units(tmp_path):
+    csrc = os.path.join(ROOT, "paper_2609_32278_amd", "csrc")
+    exe = str(tmp_path / "compact_plan")
+    cmd = ["g++", "-std=c++17", *SAN, "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include",
+           "-I" + os.path.join(ROOT, "include"), "-I" + csrc, os.path.join(ROOT, "tests", "sanitize", "compact_plan.cpp"),
+           "-L/opt/rocm/lib", "-lamdhip64", "-Wl,-rpath,/opt/rocm/lib", "-o", exe]
+    assert "passed" in _build_and_run(cmd, exe, ["2000"], tmp_path)
