@@ -57,8 +57,8 @@ __global__ __launch_bounds__(kDecodeThreads, 2) void decode_kernel(DecodeParams 
   __shared__ float o[kWaves * kRows * D], m[kWaves * kRows], l[kWaves * kRows];
   const decode::CombineShared<D, kWaves> sm{o, m, l};
   const DecodeUnit u = unit_of(p);
-  if constexpr (FP8) decode::decode_unit_fp8<D, kWaves, NT>(p.a, u, sm);
-  else decode::decode_unit<D, kWaves, NT>(p.a, u, sm);
+  if constexpr (FP8) decode::decode_unit_fp8<D, kWaves, NT, false>(p.a, u, sm);
+  else decode::decode_unit<D, kWaves, NT, false>(p.a, u, sm);
 }
 
 // Combine the parts of a split decode key range: o = sum_p e^{lse_p - M} o_p / sum_p e^{lse_p - M}.

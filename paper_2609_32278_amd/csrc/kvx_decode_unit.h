@@ -69,8 +69,10 @@ struct CombineShared {
 
 // Combine the waves' partial results through LDS and write the chunk's result.
 // Lane (n, g) holds dims 16 b + 4 g + i of row n, relative to its row maximum m_run
-// (log2 units), and the part l_run of the row sum over its own keys.
-template <int D, int NW>
+// (log2 units), and the part l_run of the row sum over its own keys.  A row whose sum is a
+// NaN (a NaN or an infinite score) is written as zeros, and as NaN with NANS, which is
+// what a prefill tile gives: one-token requests beside longer ones keep that.
+template <int D, int NW, bool NANS>
 __device__ __forceinline__ void combine_waves(const DecodeArgs& p, const DecodeUnit& u, CombineShared<D, NW> sm,
                                               const f32x4 (&o)[D / 16], float m_run, float l_run, float vscale) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -91,7 +93,7 @@ __device__ __forceinline__ void combine_waves(const DecodeArgs& p, const DecodeU
 #pragma unroll
     for (int w = 0; w < NW; w++) M = fmaxf(M, sm.m[w * kRows + row]);
     float wsum = 0.f, acc = 0.f;
-    if (M != -INFINITY) {
+    if (NANS || M != -INFINITY) {
 #pragma unroll
       for (int w = 0; w < NW; w++) {
         const float e = sm.m[w * kRows + row] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(sm.m[w * kRows + row] - M);
@@ -99,7 +101,7 @@ __device__ __forceinline__ void combine_waves(const DecodeArgs& p, const DecodeU
         acc += e * sm.o[(w * kRows + row) * D + d];
       }
     }
-    const float val = wsum > 0.f ? acc * vscale / wsum : 0.f;
+    const float val = wsum > 0.f ? acc * vscale / wsum : NANS ? acc * 0.f : 0.f;
     const float lse_v = wsum > 0.f ? (M + __log2f(wsum)) * kLn2 : -INFINITY;
     if (u.part < 0) {
       const size_t orow = (size_t)u.qo_row * p.num_q_heads + u.head * G + row;
@@ -122,7 +124,7 @@ struct PairRegs {
 };
 
 // One unit on NW waves; wave w takes page pairs w, w + NW, ...
-template <int D, int NW, bool NT>
+template <int D, int NW, bool NT, bool NANS>
 __device__ __forceinline__ void decode_unit(const DecodeArgs& p, const DecodeUnit& u, CombineShared<D, NW> sm) {
   constexpr int QS = D / 32;   // QK reduction steps
   constexpr int DB = D / 16;   // PV output blocks
@@ -265,7 +267,7 @@ __device__ __forceinline__ void decode_unit(const DecodeArgs& p, const DecodeUni
   }
   for (int j = wave; j < n_pairs; j += NW) compute(j, j + NW, r);
 
-  combine_waves<D, NW>(p, u, sm, o, m_run, l_run, 1.0f);
+  combine_waves<D, NW, NANS>(p, u, sm, o, m_run, l_run, 1.0f);
 }
 
 // ---------------------------------------------------------------- fp8 pool
@@ -290,7 +292,7 @@ struct QuadRegs {
   uint4 v[D / 16];     // V^T codes: all 16 slots of the lane's dim of page g
 };
 
-template <int D, int NW, bool NT>
+template <int D, int NW, bool NT, bool NANS>
 __device__ __forceinline__ void decode_unit_fp8(const DecodeArgs& p, const DecodeUnit& u, CombineShared<D, NW> sm) {
   constexpr int KS = D / 64;  // K loads per MFMA row block
   constexpr int DB = D / 16;  // PV output blocks
@@ -441,7 +443,7 @@ __device__ __forceinline__ void decode_unit_fp8(const DecodeArgs& p, const Decod
   int j = wave;
   for (; j < n_full; j += NW) compute(j, j + NW, r, std::false_type{});
   if (j < n_quads) compute(j, j + NW, r, std::true_type{});
-  combine_waves<D, NW>(p, u, sm, o, m_run, l_run, p.v_scale[u.head]);
+  combine_waves<D, NW, NANS>(p, u, sm, o, m_run, l_run, p.v_scale[u.head]);
 }
 
 

@@ -48,6 +48,41 @@ def test_batches_that_mix_prefill_and_decode(dt, hq, hkv, d, split, scaled_q):
                      split_keys=split, scaled_q=scaled_q)
 
 
+@pytest.mark.parametrize("dt", [wl.KV_BF16, wl.KV_FP8_E4M3])
+@pytest.mark.parametrize("d", [128, 64])
+@pytest.mark.parametrize("split", [0, 1024])
+def test_mixed_batches_keep_nan(dt, d, split):
+    """A NaN or infinity in a one-token request's query, keys or values comes out as NaN in
+    just the query heads (for values: the dim) it reaches, in a mixed batch as in a tile."""
+    hq, hkv = 32, 4
+    P, E = [9000, 4000, 15000, 700, 12345, 2048, 8000, 33], [1, 1, 1, 40, 1, 1, 1, 130]
+    w = wl.make_custom(P, E, hq, hkv, d, kv_dtype=dt, seed=65)
+    kv = [wl.request_kv(w, r, DEV) for r in range(len(P))]
+    q = [wl.request_q(w, r, DEV) for r in range(len(P))]
+    want = torch.zeros((len(P), hq, d), dtype=torch.bool)
+    q[0][0, 3] = float("nan")
+    want[0, 3] = True
+    q[5][0, 7, 0] = float("inf")  # infinite scores of both signs
+    want[5, 7] = True
+    if dt == wl.KV_BF16:          # (storing codes clamps what is not finite)
+        kv[1][0][1234, 1, 5] = float("nan")
+        want[1, 8:16] = True
+        kv[2][0][7777, 2, 9] = float("inf")  # NaN where the score is +inf, no weight where it is -inf
+        want[2, 16:24] = (q[2][0, 16:24, 9] > 0).cpu()[:, None]
+        kv[4][1][4321, 0, 11] = float("nan")
+        want[4, 0:8, 11] = True
+    run = GpuRun(w, overrides={"kv": lambda r: kv[r], "q": lambda r: q[r]}, split_keys=split)
+    try:
+        run.store()
+        out = run.attend()
+        for r in range(len(P)):
+            rows = out[int(run.qo[r]):int(run.qo[r + 1])]
+            got = torch.isnan(rows).cpu()
+            assert torch.equal(got, want[r].expand_as(got)), (r, int(got.sum()), int(want[r].sum()))
+    finally:
+        run.close()
+
+
 @pytest.mark.parametrize("dt,d", [(wl.KV_BF16, 128), (wl.KV_FP8_E4M3, 128), (wl.KV_BF16, 64), (wl.KV_FP8_E4M3, 64)])
 def test_decode_beyond_the_infinity_cache_gives_the_same_bits(dt, d):
     """A decode batch that reads more than 256 MB streams its pages with non-temporal
