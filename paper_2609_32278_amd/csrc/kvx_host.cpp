@@ -402,6 +402,16 @@ int64_t choose_split(const std::vector<Tile>& tiles, int32_t Hkv, int32_t tile_t
   return best_split;
 }
 
+// Whether the one-token suffixes of a batch become decode units next to the tiles of the
+// longer ones: when through tiles they would take a slot at least 8 iterations (below
+// that the merge of their chunks costs what they save).
+bool is_mixed_batch(const kvx_batch* b, int32_t Hq, int32_t Hkv) {
+  int64_t one_token = 0;  // iterations, all KV heads
+  for (int r = 0; r < b->num_reqs; r++)
+    if (b->extend_lens[r] == 1) one_token += Hkv * ceil_div((int64_t)b->prefix_lens[r] + 1, kvx::kTileKeys);
+  return Hq / Hkv <= kvx::kDecodeMaxGroup && one_token >= 8 * kPlanSlots;
+}
+
 // Work plan of extend_attention.
 //   * every request's suffix is cut into tiles of tile_tok tokens (x group query heads
 //     = 256 rows) per KV head; a tile covers keys [0, P + last token of the tile];
@@ -419,22 +429,14 @@ int64_t choose_split(const std::vector<Tile>& tiles, int32_t Hkv, int32_t tile_t
 //     first, which is nearly longest first and streams one request's pages at a time.  (By
 //     total work of the request, a request of few long tiles came last: 16 agents with
 //     4k-32k prefixes, 3.19 -> 2.85 ms.)
-//   * one-token suffixes next to longer ones become decode units, key chunks of the (request,
-//     KV head), when through tiles they would take a slot at least 8 iterations (below
-//     that the merge of their chunks costs what they save).
+//   * mixed: one-token suffixes become decode units, key chunks of the (request, KV head).
 int make_plan(const kvx_batch* b, const std::vector<int64_t>& qo, int32_t Hq, int32_t Hkv, int32_t D,
-              int32_t split_keys, const PartLimits& limits, bool allow_mixed, Plan& plan) {
+              int32_t split_keys, const PartLimits& limits, bool mixed, Plan& plan) {
   const int G = Hq / Hkv;
   const int tile_tok = kvx::kTileRows / G;
   const int BN = kvx::kTileKeys;
 
-  int64_t one_token = 0, one_keys = 0;  // iterations and keys of one-token suffixes, all KV heads
-  for (int r = 0; r < b->num_reqs; r++)
-    if (b->extend_lens[r] == 1) {
-      one_token += Hkv * ceil_div((int64_t)b->prefix_lens[r] + 1, BN);
-      one_keys += Hkv * ((int64_t)b->prefix_lens[r] + 1);
-    }
-  plan.mixed = allow_mixed && G <= kvx::kDecodeMaxGroup && one_token >= 8 * kPlanSlots;
+  plan.mixed = mixed;
   // requests by their longest tile
   std::vector<int32_t> order;
   for (int r = 0; r < b->num_reqs; r++)
@@ -460,6 +462,9 @@ int make_plan(const kvx_batch* b, const std::vector<int64_t>& qo, int32_t Hq, in
   plan.dec_parts = 0;
   if (plan.mixed) {
     const int64_t A = kvx::kDecodeChunkAlign;
+    int64_t one_keys = 0;  // keys of one-token suffixes, all KV heads
+    for (int r = 0; r < b->num_reqs; r++)
+      if (b->extend_lens[r] == 1) one_keys += Hkv * ((int64_t)b->prefix_lens[r] + 1);
     chunk = split_keys > 0 ? split_keys : std::min<int64_t>(2048, std::max<int64_t>(512, one_keys / 512)) / A * A;
     auto chunks_of = [&](int r) { return ceil_div((int64_t)b->prefix_lens[r] + 1, chunk); };
     for (;; chunk *= 2) {  // keep the number of parts bounded
@@ -1400,7 +1405,9 @@ int extend_attention_plan(const kvx_batch* batch, int32_t num_q_heads, int32_t n
     } else {
       Plan plan;
       if (int rc = make_plan(batch, qo, num_q_heads, num_kv_heads, head_dim, split_keys,
-                             PartLimits{kMaxParts, kMaxParts}, true, plan)) return rc;
+                             PartLimits{kMaxParts, kMaxParts}, is_mixed_batch(batch, num_q_heads, num_kv_heads),
+                             plan))
+        return rc;
       out_items = std::move(plan.items);
     }
   }
@@ -1447,22 +1454,19 @@ int kvx::attention_call(kvx_pool* pool, const kvx_batch* batch, const void* q, i
   kvx::CompactPlan compact;
   bool in_args = false;
   std::vector<uint8_t> blob;  // one upload: units, then merges, then the decode units' merges
-  for (const bool mixed : {true, false}) {
+  for (bool mixed = is_mixed_batch(batch, num_q_heads, pool->num_kv_heads);; mixed = false) {
     // in the fixed scratch, a mixed plan's decode parts have a quarter of the region
     PartLimits lim{buf.max_parts(part_bytes), buf.max_parts(dec_part_bytes)};
     if (fixed && mixed) lim = PartLimits{lim.prefill - (lim.prefill + 3) / 4, lim.decode / 4};
     plan = Plan();
     if (int rc = make_plan(batch, qo, num_q_heads, pool->num_kv_heads, D, pool->split_keys, lim, mixed, plan)) return rc;
-    if (fixed && mixed && !plan.mixed) continue;  // no decode units: the whole region for the rest
     in_args = inline_merges(plan.merges, pool->num_kv_heads, m.plan) && compact_plan(plan, compact);
-    if (in_args) {
-      blob.clear();
-      break;
-    }
+    if (in_args) break;
     m.plan.n = 0;
     blob = plan_blob(plan.units, plan.merges, plan.dec_merges);
     // a mixed plan has more units: what does not fit its region may fit without it
-    if (!(plan.mixed && fixed && blob.size() > fixed->plan_bytes)) break;
+    if (!(mixed && fixed && blob.size() > fixed->plan_bytes)) break;
+    blob.clear();
   }
   if (int rc = buf.check_plan(blob.size())) return rc;
   if (int rc = use_device(pool)) return rc;

@@ -76,7 +76,8 @@ int main(int argc, char** argv) {
       continue;
     }
     Plan plan;
-    CHECK(make_plan(&b, qo, hkv * g, hkv, 128, forced, PartLimits{kMaxParts, kMaxParts}, uni(0, 1) == 1, plan) == KVX_OK);
+    CHECK(make_plan(&b, qo, hkv * g, hkv, 128, forced, PartLimits{kMaxParts, kMaxParts},
+                    uni(0, 1) == 1 && is_mixed_batch(&b, hkv * g, hkv), plan) == KVX_OK);
     static kvx::CompactPlan c;
     if (compact_plan(plan, c)) {
       compact_plans++;

@@ -54,12 +54,26 @@ def test_short_batches_are_split_until_the_start_of_a_unit_dominates():
     assert (inner["key_end"] - inner["key_begin"] >= 256).all()
 
 
-@pytest.mark.skipif(shutil.which("g++") is None or not os.path.exists("/opt/rocm/lib/libamdhip64.so"),
-                    reason="g++ or the HIP runtime library not installed")
-def test_plans_in_kernel_arguments_expand_to_the_uploaded_units(tmp_path):
+needs_host_build = pytest.mark.skipif(
+    shutil.which("g++") is None or not os.path.exists("/opt/rocm/lib/libamdhip64.so"),
+    reason="g++ or the HIP runtime library not installed")
+
+
+def _host_check(tmp_path, name, arg, flags):
     csrc = os.path.join(ROOT, "paper_2609_32278_amd", "csrc")
-    exe = str(tmp_path / "compact_plan")
-    cmd = ["g++", "-std=c++17", *SAN, "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include",
-           "-I" + os.path.join(ROOT, "include"), "-I" + csrc, os.path.join(ROOT, "tests", "sanitize", "compact_plan.cpp"),
+    exe = str(tmp_path / name)
+    cmd = ["g++", "-std=c++17", *flags, "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include",
+           "-I" + os.path.join(ROOT, "include"), "-I" + csrc, os.path.join(ROOT, "tests", "sanitize", name + ".cpp"),
            "-L/opt/rocm/lib", "-lamdhip64", "-Wl,-rpath,/opt/rocm/lib", "-o", exe]
-    assert "passed" in _build_and_run(cmd, exe, ["2000"], tmp_path)
+    assert "passed" in _build_and_run(cmd, exe, [arg], tmp_path)
+
+
+@needs_host_build
+def test_plans_in_kernel_arguments_expand_to_the_uploaded_units(tmp_path):
+    _host_check(tmp_path, "compact_plan", "2000", SAN)
+
+
+@needs_host_build
+@pytest.mark.parametrize("what", ["once"])
+def test_planning_of_the_allocation_free_call(tmp_path, what):
+    _host_check(tmp_path, "noalloc_plan", what, ["-O2"])
