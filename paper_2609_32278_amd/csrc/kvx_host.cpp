@@ -259,7 +259,8 @@ int check_page_ids(const kvx_pool* pool, const kvx_batch* b, hipStream_t stream)
 struct Plan {
   std::vector<AttnUnit> units;  // in launch order (position i runs on XCD i % 8)
   std::vector<MergeUnit> merges;
-  std::vector<kvx_work_item> items;  // same order, for inspection
+  bool inspect = false;              // fill items: the same units in the same order, for
+  std::vector<kvx_work_item> items;  // extend_attention_plan
   int64_t n_parts = 0;
   std::vector<kvx::PlanTile> tiles;  // what the units are made of, and a code word each
   std::vector<uint32_t> codes;       // (empty if the batch is beyond their limits)
@@ -303,47 +304,101 @@ struct Filler {
   double cost = 0.0;  // of one unit
 };
 
-// Duration, in iterations, of the longest-first schedule of one KV head's units on its
-// share of the 256 workgroup slots, when the key ranges are split every `split` keys (0 = not at
-// all).  Equal units are scheduled as groups.
-double schedule_length(const std::vector<Tile>& tiles, int64_t split, int32_t Hkv, int32_t tile_tok,
-                       const UnitCosts& k, const Filler& filler, int64_t& parts) {
-  const int BN = kvx::kTileKeys;
-  std::vector<std::pair<double, int64_t>> units;  // (cost, how many)
-  auto add = [&](double c, int64_t n) {
-    if (!units.empty() && units.back().first == c) units.back().second += n;
-    else units.push_back({c, n});
-  };
-  parts = 0;
-  for (const Tile& t : tiles) {
-    const int64_t nb = split > 0 ? t.qpos0 / split : 0;  // boundaries split, 2 split, ... <= qpos0
-    const double extra = nb > 0 ? k.start + k.part * t.ntok / tile_tok : k.start;
-    if (nb > 0) {
-      add((double)(split / BN) + extra, nb);
-      parts += nb + 1;
+// The trial schedules of one search: one KV head's units on its share of the 256 workgroup
+// slots.  Planning is on the path of every call, so a trial keeps its memory, takes equal
+// units and equal slots as groups, and gives up once it cannot be the shortest (24 requests of
+// 124-239 tokens on 8/1/128 heads, 148 tiles: 500 -> 58 us a plan).
+class Trials {
+ public:
+  Trials(const std::vector<Tile>& tiles, int32_t Hkv, int32_t tile_tok, const UnitCosts& k, const Filler& filler)
+      : tiles_(tiles), tile_tok_(tile_tok), slots_(std::max<int64_t>(1, kPlanSlots / Hkv)), k_(k), filler_(filler) {}
+
+  // The units when key ranges are split every `split` keys (0 = not at all): returns the
+  // number of parts.
+  int64_t cut(int64_t split) {
+    const int BN = kvx::kTileKeys;
+    units_.clear();
+    total_ = 0.0;
+    auto add = [&](double c, int64_t n) {
+      total_ += c * (double)n;
+      if (!units_.empty() && units_.back().first == c) units_.back().second += n;
+      else units_.push_back({c, n});
+    };
+    parts_ = 0;
+    int64_t inner = 0;  // inner parts of whole tiles, all alike
+    int64_t nb = 0;     // boundaries split, 2 split, ... <= qpos0
+    for (size_t i = 0; i < tiles_.size(); i++) {
+      const Tile& t = tiles_[i];
+      // a request's tiles come longest first, a few tokens apart
+      if (split > 0 && (i == 0 || t.r != tiles_[i - 1].r)) nb = t.qpos0 / split;
+      while (nb * split > t.qpos0) nb--;
+      const double extra = nb > 0 ? k_.start + k_.part * t.ntok / tile_tok_ : k_.start;
+      if (nb > 0) {
+        if (t.ntok == tile_tok_) inner += nb;
+        else add((double)(split / BN) + extra, nb);
+        parts_ += nb + 1;
+      }
+      add((double)ceil_div(t.kend - nb * split, BN) + extra, 1);
     }
-    add((double)ceil_div(t.kend - nb * split, BN) + extra, 1);
-  }
-  if (filler.units > 0) units.push_back({filler.cost, filler.units});
-  std::sort(units.begin(), units.end(), [](const auto& x, const auto& y) { return x.first > y.first; });
-  // slots as groups of equal load, least loaded first
-  typedef std::pair<double, int64_t> Slots;
-  std::priority_queue<Slots, std::vector<Slots>, std::greater<Slots>> free;
-  free.push({0.0, std::max<int64_t>(1, kPlanSlots / Hkv)});
-  double end = 0.0;
-  for (auto [cost, n] : units) {
-    while (n > 0) {
-      Slots s = free.top();
-      free.pop();
-      const int64_t m = std::min(n, s.second);
-      if (s.second > m) free.push({s.first, s.second - m});
-      free.push({s.first + cost, m});
-      end = std::max(end, s.first + cost);
-      n -= m;
+    if (inner > 0) add((double)(split / BN) + (k_.start + k_.part * tile_tok_ / tile_tok_), inner);
+    if (filler_.units > 0) {
+      total_ += filler_.cost * (double)filler_.units;
+      units_.push_back({filler_.cost, filler_.units});
     }
+    return parts_;
   }
-  return parts > 0 ? end + k.merge : end;
-}
+
+  // Duration, in iterations, of the longest-first schedule of these units with the merge
+  // launch; or any value of at least `cap` if it is no shorter than that.
+  double length(double cap) {
+    const double merge = parts_ > 0 ? k_.merge : 0.0;
+    const double even = total_ / (double)slots_ * (1.0 - 1e-9);
+    if (even + merge >= cap) return even + merge;
+    std::sort(units_.begin(), units_.end(), [](const auto& x, const auto& y) { return x.first > y.first; });
+    // slots as groups of equal load, a heap with the least loaded first
+    heap_.assign(1, {0.0, slots_});
+    double end = 0.0;
+    for (auto [cost, n] : units_) {
+      while (n > 0) {
+        const auto [load, count] = heap_[0];
+        const int64_t m = std::min(n, count);
+        end = std::max(end, load + cost);
+        if (end + merge >= cap) return end + merge;
+        sink({load + cost, m});
+        if (count > m) rise({load, count - m});
+        n -= m;
+      }
+    }
+    return end + merge;
+  }
+
+ private:
+  typedef std::pair<double, int64_t> Group;  // cost or load, how many
+  void sink(Group g) {  // in place of the first
+    size_t i = 0;
+    for (size_t c; (c = 2 * i + 1) < heap_.size(); i = c) {
+      if (c + 1 < heap_.size() && heap_[c + 1].first < heap_[c].first) c++;
+      if (g.first <= heap_[c].first) break;
+      heap_[i] = heap_[c];
+    }
+    heap_[i] = g;
+  }
+  void rise(Group g) {
+    size_t i = heap_.size();
+    heap_.push_back(g);
+    for (size_t up; i > 0 && heap_[up = (i - 1) / 2].first > g.first; i = up) heap_[i] = heap_[up];
+    heap_[i] = g;
+  }
+
+  const std::vector<Tile>& tiles_;
+  const int32_t tile_tok_;
+  const int64_t slots_;
+  const UnitCosts k_;
+  const Filler filler_;
+  std::vector<Group> units_, heap_;
+  double total_ = 0.0;
+  int64_t parts_ = 0;
+};
 
 // Length (keys, a multiple of 64) of the parts key ranges are split into, 0 = no split.
 //   * A batch whose longest tile is at most an eighth of a slot's share of the work runs
@@ -368,31 +423,46 @@ int64_t choose_split(const std::vector<Tile>& tiles, int32_t Hkv, int32_t tile_t
   const double slots = std::max(1.0, (double)kPlanSlots / Hkv);  // per KV head
   const double share = ((double)total + filler.cost * (double)filler.units) / slots;  // iterations per slot
   if ((double)longest * 8 <= share) return 0;
-  int64_t best_split = 0, parts = 0;
-  double best = schedule_length(tiles, 0, Hkv, tile_tok, k, filler, parts);
+  constexpr double kNever = 1e300;
+  Trials trial(tiles, Hkv, tile_tok, k, filler);
+  trial.cut(0);
+  int64_t best_split = 0;
+  double best = trial.length(kNever);
   if (best <= 1.04 * (share + k.start * std::max(1.0, (double)tiles.size() / slots))) return 0;
   auto units_at = [&](int64_t len) {  // iterations per part; the count never grows with it
-    int64_t n = 0;
-    for (const Tile& t : tiles) n += t.qpos0 / (len * BN) + 1;
+    const int64_t split = len * BN;
+    int64_t n = 0, nb = 0;
+    for (size_t i = 0; i < tiles.size(); i++) {
+      const int64_t q = tiles[i].qpos0;
+      if (i == 0 || tiles[i].r != tiles[i - 1].r) nb = q / split;
+      while (nb * split > q) nb--;
+      n += nb + 1;
+    }
     return n;
   };
   auto try_length = [&](int64_t len, double margin) {
-    const double least = std::max((double)len, share + k.start * (double)units_at(len) / slots);
-    if ((least + k.merge) * margin >= best) return;  // cannot win
-    double t = schedule_length(tiles, len * BN, Hkv, tile_tok, k, filler, parts);
+    if (((double)len + k.merge) * margin >= best) return;  // cannot win
+    const int64_t parts = trial.cut(len * BN);
     if (parts == 0 || parts * Hkv > max_parts) return;
-    if ((double)parts <= slots) t += 0.06 * (double)len;
-    t *= margin;
+    const double one_round = (double)parts <= slots ? 0.06 * (double)len : 0.0;
+    const double t = (trial.length(best / margin * (1.0 + 1e-9) - one_round) + one_round) * margin;
     if (t < best) {
       best = t;
       best_split = len * BN;
     }
   };
+  double keys = 0.0;
+  for (const Tile& t : tiles) keys += (double)t.qpos0;
   for (const int rounds : {1, 2}) {
-    int64_t lo = 4, hi = longest;
+    // the shortest parts of at most this many units; a tile has more than qpos0 / part and
+    // at most qpos0 / part + 1
+    const double most = rounds * slots, rest = most - (double)tiles.size();
+    int64_t lo = std::min(longest, std::max<int64_t>(4, (int64_t)(keys / BN / most)));
+    int64_t hi = rest > 0 ? std::min<int64_t>(longest, std::max<int64_t>(4, (int64_t)(keys / BN / rest) + 2)) : longest;
+    hi = std::max(lo, hi);
     while (lo < hi) {
       const int64_t mid = lo + (hi - lo) / 2;
-      if ((double)units_at(mid) <= rounds * slots) hi = mid;
+      if ((double)units_at(mid) <= most) hi = mid;
       else lo = mid + 1;
     }
     try_length(lo, 1.0);
@@ -663,13 +733,14 @@ int make_plan(const kvx_batch* b, const std::vector<int64_t>& qo, int32_t Hq, in
   plan.units.clear();
   plan.items.clear();
   plan.units.reserve(longest * kvx::kNumXcd);
-  plan.items.reserve(longest * kvx::kNumXcd);
+  if (plan.inspect) plan.items.reserve(longest * kvx::kNumXcd);
   for (size_t i = 0; i < longest; i++) {
     for (int x = 0; x < kvx::kNumXcd; x++) {
       if (i < per_xcd[x].size()) {
         const AttnUnit& u = per_xcd[x][i].u;
         plan.units.push_back(u);
         if (coded) plan.codes.push_back(per_xcd[x][i].code);
+        if (!plan.inspect) continue;
         const bool dec = (u.head_ntok & kvx::kDecodeUnitFlag) != 0;
         // inspected part numbers are dense: decode parts follow the prefill parts
         const int32_t part = dec && u.part >= 0 ? (int32_t)plan.n_parts + u.part : u.part;
@@ -680,14 +751,14 @@ int make_plan(const kvx_batch* b, const std::vector<int64_t>& qo, int32_t Hq, in
         pad.part = -1;
         plan.units.push_back(pad);
         if (coded) plan.codes.push_back(kvx::kPlanPad);
-        plan.items.push_back(kvx_work_item{-1, 0, 0, 0, 0, 0, -1, x});
+        if (plan.inspect) plan.items.push_back(kvx_work_item{-1, 0, 0, 0, 0, 0, -1, x});
       }
     }
   }
   // drop trailing padding
   while (!plan.units.empty() && plan.units.back().key_end <= plan.units.back().key_begin) {
     plan.units.pop_back();
-    plan.items.pop_back();
+    if (plan.inspect) plan.items.pop_back();
     if (coded) plan.codes.pop_back();
   }
   if (most_ranges > (int64_t)kvx::kPlanRanges) plan.codes.clear();
@@ -701,6 +772,7 @@ using kvx::DecodeUnit;
 struct DecodePlan {
   std::vector<DecodeUnit> units;
   std::vector<DecodeMerge> merges;
+  bool inspect = false;  // as in Plan
   std::vector<kvx_work_item> items;
   int64_t n_parts = 0;
 };
@@ -770,7 +842,7 @@ int make_decode_plan(const kvx_batch* b, const std::vector<int64_t>& qo, int32_t
   std::stable_sort(plan.units.begin(), plan.units.end(), [](const DecodeUnit& x, const DecodeUnit& y) {
     return x.key_end - x.key_begin > y.key_end - y.key_begin;
   });
-  for (size_t i = 0; i < plan.units.size(); i++) {
+  for (size_t i = 0; plan.inspect && i < plan.units.size(); i++) {
     const DecodeUnit& u = plan.units[i];
     kvx_work_item it{u.req, u.head, 0, 1, u.key_begin, u.key_end, u.part, (int32_t)(i % kvx::kNumXcd)};
     plan.items.push_back(it);
@@ -1400,10 +1472,12 @@ int extend_attention_plan(const kvx_batch* batch, int32_t num_q_heads, int32_t n
   if (qo.back() > 0) {
     if (is_decode_batch(batch, num_q_heads, num_kv_heads)) {
       DecodePlan dp;
+      dp.inspect = true;
       if (int rc = make_decode_plan(batch, qo, num_kv_heads, split_keys, kMaxParts, dp)) return rc;
       out_items = std::move(dp.items);
     } else {
       Plan plan;
+      plan.inspect = true;
       if (int rc = make_plan(batch, qo, num_q_heads, num_kv_heads, head_dim, split_keys,
                              PartLimits{kMaxParts, kMaxParts}, is_mixed_batch(batch, num_q_heads, num_kv_heads),
                              plan))

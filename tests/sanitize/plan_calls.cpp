@@ -1,11 +1,12 @@
-// Host-only checks of how extend_attention_noalloc plans (kvx::attention_call with a fixed
-// scratch, csrc/kvx_host.cpp), built by tests/test_plan_schedule.py.  Planning comes before
-// any device work; the scratch has no address here, so that a call whose plan was accepted
-// ends with KVX_EHIP and no launch.  The argument names the check.
+// Host-only checks of how attention calls plan (csrc/kvx_host.cpp), built by
+// tests/test_plan_schedule.py.  The argument names the check.  extend_attention_noalloc plans
+// before any device work; its scratch has no address here, so that a call whose plan was
+// accepted ends with KVX_EHIP and no launch.
 
 #include "kvx_host.cpp"
 
 #include <chrono>
+#include <tuple>
 
 namespace kvx {
 #define KVX_STUB(name, ...) \
@@ -85,11 +86,41 @@ void check_planned_once() {
   CHECK(call < 1.5 * one);
 }
 
+// The search for a split costs at most as much as three plans of the split it found (many
+// tiles of one KV head, where a trial schedule has the most units).
+void check_search_time() {
+  for (const auto& [hq, n, p, step, e] : std::vector<std::tuple<int32_t, int, int32_t, int32_t, int32_t>>{
+           {8, 24, 10022, 155, 124}, {32, 8, 2366, 5000, 230}, {8, 7, 2593, 2350, 1050}}) {
+    std::vector<int32_t> P, E;
+    for (int r = 0; r < n; r++) {
+      P.push_back(p + step * r);
+      E.push_back(e + 5 * r);
+    }
+    const TestBatch t(P, E);
+    int64_t count = 0;
+    CHECK(extend_attention_plan(&t.b, hq, 1, 128, 0, nullptr, 0, &count) == KVX_OK);
+    std::vector<kvx_work_item> items((size_t)count);
+    CHECK(extend_attention_plan(&t.b, hq, 1, 128, 0, items.data(), count, &count) == KVX_OK);
+    int32_t split = 0;
+    for (const kvx_work_item& i : items)
+      if (i.part >= 0 && i.key_begin == 0) split = i.key_end;
+    CHECK(split > 0);
+    double forced = 1e30, found = 1e30;
+    for (int i = 0; i < 20; i++) {
+      forced = std::min(forced, least_us([&] { extend_attention_plan(&t.b, hq, 1, 128, split, nullptr, 0, &count); }, 5));
+      found = std::min(found, least_us([&] { extend_attention_plan(&t.b, hq, 1, 128, 0, nullptr, 0, &count); }, 5));
+    }
+    std::printf("forced %.0f us, found %.0f us\n", forced, found);
+    CHECK(found < 4.0 * forced);
+  }
+}
+
 }  // namespace
 
 int main(int argc, char** argv) {
   const std::string what = argv[argc - 1];
   if (what == "once") check_planned_once();
+  else if (what == "search") check_search_time();
   else return 2;
   std::printf("passed\n");
   return 0;
