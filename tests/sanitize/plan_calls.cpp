@@ -115,12 +115,53 @@ void check_search_time() {
   }
 }
 
+// With few parts allowed, the split chosen makes a schedule within a tenth of the best one
+// among all lengths that keep within them.
+void check_limited_splits() {
+  struct Shape {
+    int32_t hq, hkv, d, n, p0, p1, e0, e1;
+  };
+  const Shape shapes[] = {{32, 8, 128, 3, 37701, 48480, 313, 494}, {16, 1, 128, 5, 29560, 44412, 424, 1018},
+                          {8, 1, 128, 19, 34942, 48111, 233, 250}, {40, 10, 128, 3, 46465, 49414, 298, 339},
+                          {4, 2, 64, 2, 21610, 88566, 90, 3157},   {64, 8, 128, 40, 1000, 60000, 10, 300}};
+  int limited = 0;
+  for (const Shape& h : shapes) {
+    const int32_t tile_tok = kvx::kTileRows / (h.hq / h.hkv);
+    std::vector<Tile> tiles;
+    for (int32_t r = 0; r < h.n; r++) {
+      const int64_t P = h.p0 + (int64_t)(h.p1 - h.p0) * r / (h.n - 1), E = h.e0 + (int64_t)(h.e1 - h.e0) * (r * 7 % h.n) / (h.n - 1);
+      for (int64_t t0 = (E - 1) / tile_tok * tile_tok; t0 >= 0; t0 -= tile_tok) {
+        const int64_t n = std::min<int64_t>(tile_tok, E - t0);
+        tiles.push_back(Tile{r, (int32_t)t0, (int32_t)n, P + t0 + n, P + t0});
+      }
+    }
+    const int64_t max_parts = KVX_NOALLOC_PARTS_BYTES / ((int64_t)kvx::kTileRows * (h.d + 1) * 4);
+    Trials trial(tiles, h.hkv, tile_tok, h.d == 128 ? kUnitCosts128 : kUnitCosts64, Filler{});
+    const int64_t split = choose_split(tiles, h.hkv, tile_tok, h.d, Filler{}, max_parts);
+    CHECK(trial.cut(split) * h.hkv <= max_parts);
+    const double got = trial.length(1e300);
+    trial.cut(0);
+    double best = trial.length(1e300);
+    int64_t most = 0;
+    for (int64_t len = 4; len * 64 <= h.p1 + h.e1; len++) {
+      const int64_t parts = trial.cut(len * 64) * h.hkv;
+      most = std::max(most, parts);
+      if (parts <= max_parts) best = std::min(best, trial.length(1e300));
+    }
+    limited += choose_split(tiles, h.hkv, tile_tok, h.d, Filler{}, kMaxParts) != split;
+    std::printf("%d/%d heads: schedule %.0f, best %.0f, split %lld\n", h.hq, h.hkv, got, best, (long long)split);
+    CHECK(got <= 1.1 * best);
+  }
+  CHECK(limited >= 3);
+}
+
 }  // namespace
 
 int main(int argc, char** argv) {
   const std::string what = argv[argc - 1];
   if (what == "once") check_planned_once();
   else if (what == "search") check_search_time();
+  else if (what == "limits") check_limited_splits();
   else return 2;
   std::printf("passed\n");
   return 0;
