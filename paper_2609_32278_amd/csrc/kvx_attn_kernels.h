@@ -580,8 +580,8 @@ __device__ __forceinline__ bool run_decode_unit(const AttnParams& p, uint8_t* o_
   d.group = p.group;
   d.scale_log2 = p.scale_log2;
   const decode::CombineShared<D, kWaves> sm{(float*)o_lds, (float*)ml_lds, (float*)ml_lds + kWaves * decode::kRows};
-  if constexpr (FP8) decode::decode_unit_fp8<D, kWaves, false, true>(d, u, sm);
-  else decode::decode_unit<D, kWaves, false, true>(d, u, sm);
+  if constexpr (FP8) decode::decode_unit_fp8<D, kWaves, true>(d, u, sm, decode::PlainLoads{});
+  else decode::decode_unit<D, kWaves, true>(d, u, sm, decode::PlainLoads{});
   return true;
 }
 

@@ -52,13 +52,40 @@ __device__ __forceinline__ DecodeUnit unit_of(const DecodeParams& p) {
   return u;
 }
 
+// Whether another request's page list holds this chunk's first page at the same place
+// (prefixes are shared in whole pages from the start).  Uniform; at most four lists per lane.
+__device__ __forceinline__ bool chunk_is_shared(const DecodeParams& p, const DecodeUnit& u) {
+  const int32_t* base = p.lists.base;
+  if (base == nullptr)
+    base = (const int32_t*)((const __attribute__((address_space(4))) char*)__builtin_amdgcn_kernarg_segment_ptr() +
+                            offsetof(DecodeParams, lists.in_args));
+  const int lp = u.key_begin / kPageSize, own = ((decode::const_i32_ptr)p.a.page_ids)[u.page_base + lp];
+  bool same = false;
+#pragma unroll
+  for (int j = 0; j < kShareReqs / 64; j++) {
+    const int i = (threadIdx.x & 63) + 64 * j;
+    if (i >= p.lists.n) continue;
+    const int b = base[i];
+    if (b != u.page_base && lp < base[i + 1] - b) same |= p.a.page_ids[b + lp] == own;
+  }
+  return __any(same);
+}
+
+// NT: a chunk whose pages one request alone holds is read with non-temporal loads, which
+// spares the caches for the others; pages of a shared prefix are read again by every request
+// that holds them, mostly out of the XCD's L2, and keep plain loads.  us per call plain / all
+// non-temporal / told apart: 64 agents of 16k private tokens, 32/8/128 heads, 745 / 682 / 667;
+// 128 agents on one 16k prefix 718 / 928 / 728, on 16 of them 760 / 1075 / 751, on one of 4k
+// with 4k private tokens each 564 / 554 / 523; 128 on one of 64k, fp8 pool, 64/8/128 heads,
+// 1176 / 1997 / 1188.
 template <int D, bool FP8, bool NT>
 __global__ __launch_bounds__(kDecodeThreads, 2) void decode_kernel(DecodeParams p) {
   __shared__ float o[kWaves * kRows * D], m[kWaves * kRows], l[kWaves * kRows];
   const decode::CombineShared<D, kWaves> sm{o, m, l};
   const DecodeUnit u = unit_of(p);
-  if constexpr (FP8) decode::decode_unit_fp8<D, kWaves, NT, false>(p.a, u, sm);
-  else decode::decode_unit<D, kWaves, NT, false>(p.a, u, sm);
+  auto nt = [&]() { return NT && !chunk_is_shared(p, u); };
+  if constexpr (FP8) decode::decode_unit_fp8<D, kWaves, false>(p.a, u, sm, nt);
+  else decode::decode_unit<D, kWaves, false>(p.a, u, sm, nt);
 }
 
 // Combine the parts of a split decode key range: o = sum_p e^{lse_p - M} o_p / sum_p e^{lse_p - M}.
@@ -140,12 +167,8 @@ __global__ __launch_bounds__(256) void decode_merge_kernel(DecodeMergeParams p) 
 
 template <int D, bool FP8>
 static void launch_decode_for(const DecodeParams& p, int64_t n_units, hipStream_t stream) {
-  // K/V beyond the 256 MB Infinity Cache are read once and kept by no cache: non-temporal
-  // loads (128 agents, 6.9 GB: 1125 -> 1085 us; fp8, 3.1 GB: 567 -> 551 us, calls).  Smaller
-  // batches may find pages there that were just stored or read (48 MB: 30.4 us, 31.8 us
-  // non-temporal).
   const dim3 grid((unsigned)n_units), block(kDecodeThreads);
-  if (p.kv_bytes > (256ll << 20)) hipLaunchKernelGGL((decode_kernel<D, FP8, true>), grid, block, 0, stream, p);
+  if (p.lists.n > 0) hipLaunchKernelGGL((decode_kernel<D, FP8, true>), grid, block, 0, stream, p);
   else hipLaunchKernelGGL((decode_kernel<D, FP8, false>), grid, block, 0, stream, p);
 }
 

@@ -123,9 +123,14 @@ struct PairRegs {
   uint2 va[D / 16], vb[D / 16];  // V^T: slots 4g..4g+3 of each page, one per 16-dim block
 };
 
-// One unit on NW waves; wave w takes page pairs w, w + NW, ...
-template <int D, int NW, bool NT, bool NANS>
-__device__ __forceinline__ void decode_unit(const DecodeArgs& p, const DecodeUnit& u, CombineShared<D, NW> sm) {
+struct PlainLoads {
+  __device__ bool operator()() const { return false; }
+};
+
+// One unit on NW waves; wave w takes page pairs w, w + NW, ...  nt: asked once the first
+// (plain) loads are on their way, whether to read the further pages non-temporally; uniform.
+template <int D, int NW, bool NANS, class Nt>
+__device__ __forceinline__ void decode_unit(const DecodeArgs& p, const DecodeUnit& u, CombineShared<D, NW> sm, Nt&& nt) {
   constexpr int QS = D / 32;   // QK reduction steps
   constexpr int DB = D / 16;   // PV output blocks
   constexpr int PAGE_ELEMS = kPageSize * D;
@@ -160,7 +165,8 @@ __device__ __forceinline__ void decode_unit(const DecodeArgs& p, const DecodeUni
     pa = (size_t)(uint32_t)pages[la] * page_stride + head_off;
     pb = (size_t)(uint32_t)pages[lb] * page_stride + head_off;
   };
-  auto load_k = [&](size_t pa, size_t pb, PairRegs<D>& r) {
+  auto load_k = [&](size_t pa, size_t pb, PairRegs<D>& r, auto nt_flag) {
+    constexpr bool NT = decltype(nt_flag)::value;
     const uint16_t* k = (const uint16_t*)p.k_pool;
 #pragma unroll
     for (int s = 0; s < QS; s++) {
@@ -168,7 +174,8 @@ __device__ __forceinline__ void decode_unit(const DecodeArgs& p, const DecodeUni
       r.kb[s] = load16<NT>(k + pb + n * D + 32 * s + 8 * g);
     }
   };
-  auto load_v = [&](size_t pa, size_t pb, PairRegs<D>& r) {
+  auto load_v = [&](size_t pa, size_t pb, PairRegs<D>& r, auto nt_flag) {
+    constexpr bool NT = decltype(nt_flag)::value;
     const uint16_t* v = (const uint16_t*)p.v_pool;
 #pragma unroll
     for (int b = 0; b < DB; b++) {
@@ -186,7 +193,7 @@ __device__ __forceinline__ void decode_unit(const DecodeArgs& p, const DecodeUni
   // Pair `pair` from r; the registers are refilled with pair `next` (if < n_pairs)
   // as soon as the products have read them, so the loads of the next pair are in
   // flight for the rest of this one.
-  auto compute = [&](int pair, int next, PairRegs<D>& r) {
+  auto compute = [&](int pair, int next, PairRegs<D>& r, auto nt_flag) {
     size_t na = 0, nb = 0;
     const bool more = next < n_pairs;  // uniform
     if (more) blocks(next, na, nb);
@@ -196,14 +203,14 @@ __device__ __forceinline__ void decode_unit(const DecodeArgs& p, const DecodeUni
       sa = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, r.ka[s]), qf[s], sa, 0, 0, 0);
       sb = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, r.kb[s]), qf[s], sb, 0, 0, 0);
     }
-    if (more) load_k(na, nb, r);
+    if (more) load_k(na, nb, r, nt_flag);
     uint2 va[DB], vb[DB];
 #pragma unroll
     for (int b = 0; b < DB; b++) {
       va[b] = r.va[b];
       vb[b] = r.vb[b];
     }
-    if (more) load_v(na, nb, r);
+    if (more) load_v(na, nb, r, nt_flag);
     // keys of this lane: 4g + i of page a (key0) and of page b (key0 + 16)
     const int key0 = u.key_begin + 32 * pair + 4 * g;
     const bool tail = u.key_begin + 32 * (pair + 1) > u.key_end;  // uniform
@@ -262,10 +269,13 @@ __device__ __forceinline__ void decode_unit(const DecodeArgs& p, const DecodeUni
   if (wave < n_pairs) {
     size_t pa, pb;
     blocks(wave, pa, pb);
-    load_k(pa, pb, r);
-    load_v(pa, pb, r);
+    load_k(pa, pb, r, std::false_type{});
+    load_v(pa, pb, r, std::false_type{});
   }
-  for (int j = wave; j < n_pairs; j += NW) compute(j, j + NW, r);
+  if (nt())
+    for (int j = wave; j < n_pairs; j += NW) compute(j, j + NW, r, std::true_type{});
+  else
+    for (int j = wave; j < n_pairs; j += NW) compute(j, j + NW, r, std::false_type{});
 
   combine_waves<D, NW, NANS>(p, u, sm, o, m_run, l_run, 1.0f);
 }
@@ -292,8 +302,9 @@ struct QuadRegs {
   uint4 v[D / 16];     // V^T codes: all 16 slots of the lane's dim of page g
 };
 
-template <int D, int NW, bool NT, bool NANS>
-__device__ __forceinline__ void decode_unit_fp8(const DecodeArgs& p, const DecodeUnit& u, CombineShared<D, NW> sm) {
+template <int D, int NW, bool NANS, class Nt>
+__device__ __forceinline__ void decode_unit_fp8(const DecodeArgs& p, const DecodeUnit& u, CombineShared<D, NW> sm,
+                                                Nt&& nt) {
   constexpr int KS = D / 64;  // K loads per MFMA row block
   constexpr int DB = D / 16;  // PV output blocks
   const int lane = threadIdx.x & 63;
@@ -337,14 +348,16 @@ __device__ __forceinline__ void decode_unit_fp8(const DecodeArgs& p, const Decod
     return high ? hi : lo;
   };
   const bool k_odd = n & 4, k_high = n & 8, v_odd = g & 1, v_high = g & 2;
-  auto load_k = [&](const ids_t& w, QuadRegs<D>& r) {
+  auto load_k = [&](const ids_t& w, QuadRegs<D>& r, auto nt_flag) {
+    constexpr bool NT = decltype(nt_flag)::value;
     const char* src = kbase + (uint64_t)pick(w, k_odd, k_high) * page_bytes;
 #pragma unroll
     for (int j = 0; j < 4; j++)
 #pragma unroll
       for (int i = 0; i < KS; i++) r.k[j][i] = load16<NT>(src + 4 * j * D + 64 * i);
   };
-  auto load_v = [&](const ids_t& w, QuadRegs<D>& r) {
+  auto load_v = [&](const ids_t& w, QuadRegs<D>& r, auto nt_flag) {
+    constexpr bool NT = decltype(nt_flag)::value;
     const char* src = vbase + (uint64_t)pick(w, v_odd, v_high) * page_bytes;
 #pragma unroll
     for (int b = 0; b < DB; b++) r.v[b] = load16<NT>(src + 256 * b);
@@ -360,7 +373,7 @@ __device__ __forceinline__ void decode_unit_fp8(const DecodeArgs& p, const Decod
   // soon as the products have read them.  TAIL: the quad reaches past key_end.  (A template
   // flag and not a branch: masking the loaded registers in place inside the loop made
   // the compiler reuse some of them too early.)
-  auto compute = [&](int quad, int next, QuadRegs<D>& r, auto tail_flag) {
+  auto compute = [&](int quad, int next, QuadRegs<D>& r, auto tail_flag, auto nt_flag) {
     constexpr bool TAIL = decltype(tail_flag)::value;
     const bool more = next < n_quads;  // uniform
     ids_t nx{};
@@ -378,7 +391,7 @@ __device__ __forceinline__ void decode_unit_fp8(const DecodeArgs& p, const Decod
                                                        qf[i][1], s[j], 0, 0, 0);
       }
     }
-    if (more) load_k(nx, r);
+    if (more) load_k(nx, r, nt_flag);
     const int key0 = u.key_begin + 64 * quad + 16 * g;  // slot 0 of the lane group's page
     if constexpr (TAIL) {
 #pragma unroll
@@ -430,19 +443,22 @@ __device__ __forceinline__ void decode_unit_fp8(const DecodeArgs& p, const Decod
       o[b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, fp8x8_bf16(make_uint2(c.z, c.w))), pb,
                                                      o[b], 0, 0, 0);
     }
-    if (more) load_v(nx, r);
+    if (more) load_v(nx, r, nt_flag);
   };
 
   QuadRegs<D> r;
   if (wave < n_quads) {
     const ids_t w = ids_of(wave);
-    load_k(w, r);
-    load_v(w, r);
+    load_k(w, r, std::false_type{});
+    load_v(w, r, std::false_type{});
   }
   const int n_full = (u.key_end - u.key_begin) / (4 * kPageSize);  // at most the last quad is not full
   int j = wave;
-  for (; j < n_full; j += NW) compute(j, j + NW, r, std::false_type{});
-  if (j < n_quads) compute(j, j + NW, r, std::true_type{});
+  if (nt())
+    for (; j < n_full; j += NW) compute(j, j + NW, r, std::false_type{}, std::true_type{});
+  else
+    for (; j < n_full; j += NW) compute(j, j + NW, r, std::false_type{}, std::false_type{});
+  if (j < n_quads) compute(j, j + NW, r, std::true_type{}, std::false_type{});
   combine_waves<D, NW, NANS>(p, u, sm, o, m_run, l_run, p.v_scale[u.head]);
 }
 

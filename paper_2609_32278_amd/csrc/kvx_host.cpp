@@ -1027,6 +1027,12 @@ bool inline_store_reqs(const kvx_batch* b, const std::vector<int64_t>& qo, kvx::
   return rq.n > 0;
 }
 
+// A decode batch that reads more K/V than the 256 MB Infinity Cache holds may use non-temporal
+// loads (see decode_kernel).  Smaller batches find pages there that were just stored or read
+// (48 MB: 30.4 us, 31.8 us non-temporal), and in one of more than kShareReqs requests the look at
+// every page list would cost each unit more than these loads give.
+constexpr int64_t kStreamBytes = 256ll << 20;
+
 int decode_attention(kvx_pool* pool, const kvx_batch* batch, const std::vector<int64_t>& qo, const void* q,
                      int32_t num_q_heads, float sm_scale, void* out, float* lse, hipStream_t s, CallBuffers& buf) {
   const int D = pool->head_dim;
@@ -1042,6 +1048,29 @@ int decode_attention(kvx_pool* pool, const kvx_batch* batch, const std::vector<i
   if (!in_args) {
     dp.plan.n = m.plan.n = 0;
     blob = plan_blob(plan.units, plan.merges);
+  }
+  int64_t kv_bytes = 0;  // K and V, page lists that share pages counted each
+  std::vector<int32_t> lists;
+  for (int r = 0; r < batch->num_reqs; r++) {
+    if (batch->extend_lens[r] != 1) continue;
+    kv_bytes += 2 * ((int64_t)batch->prefix_lens[r] + 1) * pool->num_kv_heads * D * pool->elem_bytes;
+    lists.push_back(batch->page_indptr[r]);
+  }
+  const bool streams = kv_bytes > kStreamBytes && lists.size() <= (size_t)kvx::kShareReqs;
+  dp.lists.base = nullptr;
+  dp.lists.n = streams ? (int32_t)lists.size() : 0;
+  const size_t lists_at = blob.size();
+  if (streams) {
+    lists.push_back(batch->page_indptr[batch->num_reqs]);
+    const size_t bytes = lists.size() * sizeof(int32_t);
+    if (in_args) {
+      std::memcpy(dp.lists.in_args, lists.data(), bytes);  // no more requests than units
+    } else if (!buf.fixed || lists_at + bytes <= buf.fixed->plan_bytes) {
+      blob.resize(lists_at + bytes);
+      std::memcpy(blob.data() + lists_at, lists.data(), bytes);
+    } else {
+      dp.lists.n = 0;
+    }
   }
   if (int rc = buf.check_plan(blob.size())) return rc;
   if (int rc = use_device(pool)) return rc;
@@ -1070,10 +1099,7 @@ int decode_attention(kvx_pool* pool, const kvx_batch* batch, const std::vector<i
   p.num_kv_heads = pool->num_kv_heads;
   p.group = num_q_heads / pool->num_kv_heads;
   p.scale_log2 = sm_scale * 1.4426950408889634f;
-  dp.kv_bytes = 0;
-  for (int r = 0; r < batch->num_reqs; r++)
-    if (batch->extend_lens[r] == 1)
-      dp.kv_bytes += 2 * ((int64_t)batch->prefix_lens[r] + 1) * pool->num_kv_heads * D * pool->elem_bytes;
+  if (!in_args && dp.lists.n > 0) dp.lists.base = (const int32_t*)((const uint8_t*)dev + lists_at);
   hipError_t e = kvx::launch_decode(dp, (int64_t)plan.units.size(), D, pool->kv_dtype == KVX_KV_FP8_E4M3, s);
   if (e != hipSuccess) return hip_fail(e, "decode kernel launch");
   if (!plan.merges.empty()) {

@@ -278,11 +278,21 @@ struct DecodeArgs {
   float scale_log2;
 };
 
+// Page lists of the requests that decode in a batch read with non-temporal loads, to tell
+// pages that several of them hold from a request's own: list i is page_ids[base[i]] up to
+// base[i + 1].
+constexpr int kShareReqs = 256;
+struct DecodeLists {
+  const int32_t* base;               // device [n + 1], or null: in_args
+  int32_t n;                         // 0: plain loads throughout
+  int32_t in_args[kInlineUnits + 1];
+};
+
 struct DecodeParams {
   DecodeArgs a;
   const DecodeUnit* units;
-  int64_t kv_bytes;       // K and V bytes the batch reads
-  InlinePlan<DecodeUnit> plan;  // plan.n > 0: the units
+  DecodeLists lists;
+  InlinePlan<DecodeUnit> plan;  // plan.n > 0: the units (and lists.in_args the lists)
 };
 static_assert(sizeof(DecodeParams) <= 4096, "kernel arguments");
 
