@@ -515,8 +515,10 @@ bool is_mixed_batch(const kvx_batch* b, int32_t Hq, int32_t Hkv) {
 //     total work of the request, a request of few long tiles came last: 16 agents with
 //     4k-32k prefixes, 3.19 -> 2.85 ms.)
 //   * mixed: one-token suffixes become decode units, key chunks of the (request, KV head).
+//   * packed: the smallest plan there is, without padding and with no split but a forced one; a
+//     unit then runs on whatever XCD its place gives it.
 int make_plan(const kvx_batch* b, const std::vector<int64_t>& qo, int32_t Hq, int32_t Hkv, int32_t D,
-              int32_t split_keys, const PartLimits& limits, bool mixed, Plan& plan) {
+              int32_t split_keys, const PartLimits& limits, bool mixed, Plan& plan, bool packed = false) {
   const int G = Hq / Hkv;
   const int tile_tok = kvx::kTileRows / G;
   const int BN = kvx::kTileKeys;
@@ -586,7 +588,7 @@ int make_plan(const kvx_batch* b, const std::vector<int64_t>& qo, int32_t Hq, in
     filler.cost = (double)(one_keys / BN) / (double)dec_units.size() * kDecodePerIter + kUnitCosts128.start;
   }
 
-  int64_t split = split_keys > 0 ? split_keys : choose_split(tiles, Hkv, tile_tok, D, filler, limits.prefill);
+  int64_t split = split_keys > 0 || packed ? split_keys : choose_split(tiles, Hkv, tile_tok, D, filler, limits.prefill);
   auto boundaries = [&](const Tile& t) { return split > 0 ? t.qpos0 / split : 0; };  // split, 2 split, ... <= qpos0
   while (split > 0) {  // keep the number of parts bounded
     int64_t parts = 0;
@@ -761,7 +763,7 @@ int make_plan(const kvx_batch* b, const std::vector<int64_t>& qo, int32_t Hq, in
         const int32_t part = dec && u.part >= 0 ? (int32_t)plan.n_parts + u.part : u.part;
         plan.items.push_back(kvx_work_item{u.req, u.head_ntok >> 16, per_xcd[x][i].tok0, u.head_ntok & 0x7FFF,
                                            u.key_begin, u.key_end, part, x});
-      } else {
+      } else if (!packed) {
         AttnUnit pad{};
         pad.part = -1;
         plan.units.push_back(pad);
@@ -1569,18 +1571,24 @@ int kvx::attention_call(kvx_pool* pool, const kvx_batch* batch, const void* q, i
   kvx::CompactPlan compact;
   bool in_args = false;
   std::vector<uint8_t> blob;  // one upload: units, then merges, then the decode units' merges
-  for (bool mixed = is_mixed_batch(batch, num_q_heads, pool->num_kv_heads);; mixed = false) {
+  bool mixed = is_mixed_batch(batch, num_q_heads, pool->num_kv_heads), packed = false;
+  for (;;) {
     // in the fixed scratch, a mixed plan's decode parts have a quarter of the region
     PartLimits lim{buf.max_parts(part_bytes), buf.max_parts(dec_part_bytes)};
     if (fixed && mixed) lim = PartLimits{lim.prefill - (lim.prefill + 3) / 4, lim.decode / 4};
     plan = Plan();
-    if (int rc = make_plan(batch, qo, num_q_heads, pool->num_kv_heads, D, pool->split_keys, lim, mixed, plan)) return rc;
+    if (int rc = make_plan(batch, qo, num_q_heads, pool->num_kv_heads, D, pool->split_keys, lim, mixed, plan, packed))
+      return rc;
     in_args = inline_merges(plan.merges, pool->num_kv_heads, m.plan) && compact_plan(plan, compact);
     if (in_args) break;
     m.plan.n = 0;
     blob = plan_blob(plan.units, plan.merges, plan.dec_merges);
-    // a mixed plan has more units: what does not fit its region may fit without it
-    if (!(mixed && fixed && blob.size() > fixed->plan_bytes)) break;
+    // what does not fit its region may fit with tiles for the one-token suffixes (fewer units),
+    // or else packed (a batch of one long request and 40000 short ones may have most of the
+    // short ones on one XCD, and seven paddings to each)
+    if (packed || !fixed || blob.size() <= fixed->plan_bytes) break;
+    packed = !mixed;
+    mixed = false;
     blob.clear();
   }
   if (int rc = buf.check_plan(blob.size())) return rc;

@@ -155,6 +155,34 @@ void check_limited_splits() {
   CHECK(limited >= 3);
 }
 
+// The allocation-free entry point takes every batch whose units alone fit its plan region.
+void check_all_that_fits() {
+  struct Shape {
+    int32_t hq, hkv, P, E, n, p, e;  // one long request, n short ones
+  };
+  const int64_t room = KVX_NOALLOC_PLAN_BYTES / (int64_t)sizeof(AttnUnit);
+  int packed = 0;
+  for (const Shape& h : {Shape{8, 1, 98740, 242150, 116000, 60, 2}, Shape{8, 1, 131072, 75000, 60000, 40, 3},
+                         Shape{32, 1, 2104, 182903, 103000, 1000, 2}, Shape{8, 2, 98979, 15359, 78000, 60, 9},
+                         Shape{4, 2, 100000, 180000, 80000, 30, 3}, Shape{8, 8, 4295, 2000, 32000, 30, 2}}) {
+    std::vector<int32_t> P{h.P}, E{h.E};
+    const int32_t tile_tok = kvx::kTileRows / (h.hq / h.hkv);
+    int64_t units = ((int64_t)h.E + tile_tok - 1) / tile_tok * h.hkv;
+    for (int32_t r = 0; r < h.n; r++) {
+      P.push_back(r % h.p);
+      E.push_back(1 + r % h.e);
+      units += h.hkv;
+    }
+    const TestBatch t(P, E);
+    int64_t n = 0;
+    CHECK(units <= room && extend_attention_plan(&t.b, h.hq, h.hkv, 128, 0, nullptr, 0, &n) == KVX_OK);
+    packed += n > room;
+    std::printf("%lld units, %lld with padding\n", (long long)units, (long long)n);
+    CHECK(plan_noalloc(t, h.hq, h.hkv, 128) == KVX_EHIP);
+  }
+  CHECK(packed >= 2);
+}
+
 }  // namespace
 
 int main(int argc, char** argv) {
@@ -162,6 +190,7 @@ int main(int argc, char** argv) {
   if (what == "once") check_planned_once();
   else if (what == "search") check_search_time();
   else if (what == "limits") check_limited_splits();
+  else if (what == "fits") check_all_that_fits();
   else return 2;
   std::printf("passed\n");
   return 0;

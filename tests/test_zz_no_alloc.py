@@ -83,3 +83,32 @@ def test_noalloc_refuses_a_plan_larger_than_its_scratch():
         assert bool((out[:: 4096].float() == 3.0).all())
     finally:
         kvx.kv_pool_destroy(pool)
+
+
+def test_noalloc_takes_a_batch_that_fits_only_without_padding():
+    """One long request and 80000 short ones: with its XCDs evened out by padding the plan is
+    larger than the scratch; the call runs it packed, to the same bits."""
+    hq, hkv, d, n = 4, 2, 64, 80000
+    P = np.append(100000, np.arange(n) % 30)
+    E = np.append(180000, 2 + np.arange(n) % 3)
+    indptr = np.concatenate([[0], np.cumsum((P + E + 15) // 16)])
+    pool = kvx.kv_pool_create(int(indptr[-1]), 16, hkv, d)
+    try:
+        print(f"[noalloc] packed: {n + 1} requests, {indptr[-1]} pages", flush=True)
+        g = torch.Generator(device=DEV).manual_seed(45)
+        ids = np.arange(indptr[-1], dtype=np.int32)
+        k, v = [torch.randn((len(ids), hkv, 16, d), generator=g, device=DEV, dtype=torch.bfloat16) for _ in range(2)]
+        kvx.kv_pool_write_pages(pool, ids, k, v)
+        b = kvx.Batch(P, E, indptr, torch.from_numpy(ids).to(DEV))
+        items = kvx.extend_attention_plan(b, hq, hkv, d)
+        assert len(items) * 32 > kvx.NOALLOC_PLAN_BYTES > (items["req"] >= 0).sum() * 32
+        assert (items["part"] < 0).all()
+        q = torch.randn((int(E.sum()), hq, d), generator=g, device=DEV, dtype=torch.bfloat16)
+        want, got = torch.empty_like(q), torch.full_like(q, float("nan"))
+        kvx.extend_attention(pool, b, q, hq, d ** -0.5, want)
+        torch.cuda.synchronize()
+        kvx.extend_attention_noalloc(pool, b, q, hq, d ** -0.5, got)
+        torch.cuda.synchronize()
+        assert torch.equal(got.view(torch.int16), want.view(torch.int16))
+    finally:
+        kvx.kv_pool_destroy(pool)
