@@ -275,6 +275,12 @@ struct Plan {
 struct PartLimits {
   int64_t prefill, decode;
 };
+// Those of a call on the pool's workspace: the rows of kMaxParts tiles in all, decode parts
+// counting a sixteenth.
+static_assert(kvx::kTileRows == 16 * kvx::kDecodeMaxGroup, "rows of a part");
+constexpr PartLimits pool_limits(bool mixed) {
+  return PartLimits{mixed ? kMaxParts - kMaxParts / 16 : kMaxParts, kMaxParts};
+}
 
 // A tile of suffix tokens of one request; every KV head has the same tiles.
 struct Tile {
@@ -1521,9 +1527,8 @@ int extend_attention_plan(const kvx_batch* batch, int32_t num_q_heads, int32_t n
     } else {
       Plan plan;
       plan.inspect = true;
-      if (int rc = make_plan(batch, qo, num_q_heads, num_kv_heads, head_dim, split_keys,
-                             PartLimits{kMaxParts, kMaxParts}, is_mixed_batch(batch, num_q_heads, num_kv_heads),
-                             plan))
+      const bool mixed = is_mixed_batch(batch, num_q_heads, num_kv_heads);
+      if (int rc = make_plan(batch, qo, num_q_heads, num_kv_heads, head_dim, split_keys, pool_limits(mixed), mixed, plan))
         return rc;
       out_items = std::move(plan.items);
     }
@@ -1573,9 +1578,12 @@ int kvx::attention_call(kvx_pool* pool, const kvx_batch* batch, const void* q, i
   std::vector<uint8_t> blob;  // one upload: units, then merges, then the decode units' merges
   bool mixed = is_mixed_batch(batch, num_q_heads, pool->num_kv_heads), packed = false;
   for (;;) {
-    // in the fixed scratch, a mixed plan's decode parts have a quarter of the region
-    PartLimits lim{buf.max_parts(part_bytes), buf.max_parts(dec_part_bytes)};
-    if (fixed && mixed) lim = PartLimits{lim.prefill - (lim.prefill + 3) / 4, lim.decode / 4};
+    PartLimits lim = pool_limits(mixed);
+    if (fixed) {
+      lim = PartLimits{buf.max_parts(part_bytes), buf.max_parts(dec_part_bytes)};
+      // in the fixed scratch, a mixed plan's decode parts have a quarter of the region
+      if (mixed) lim = PartLimits{lim.prefill - (lim.prefill + 3) / 4, lim.decode / 4};
+    }
     plan = Plan();
     if (int rc = make_plan(batch, qo, num_q_heads, pool->num_kv_heads, D, pool->split_keys, lim, mixed, plan, packed))
       return rc;

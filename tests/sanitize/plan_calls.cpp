@@ -183,6 +183,22 @@ void check_all_that_fits() {
   CHECK(packed >= 2);
 }
 
+// The partial results of a mixed batch, of both kinds together, stay within those of kMaxParts
+// tiles (the 2 GiB that kvx.h states).
+void check_bound_on_parts() {
+  const TestBatch t({64 * 16000, 64 * 16000, 64 * 300}, {32, 1, 1});
+  int64_t n = 0;
+  CHECK(extend_attention_plan(&t.b, 8, 1, 128, 64, nullptr, 0, &n) == KVX_OK);
+  std::vector<kvx_work_item> items((size_t)n);
+  CHECK(extend_attention_plan(&t.b, 8, 1, 128, 64, items.data(), n, &n) == KVX_OK);
+  int64_t prefill = 0, decode = 0;
+  for (const kvx_work_item& i : items)
+    if (i.part >= 0) (i.req == 0 ? prefill : decode) += 1;
+  std::printf("%lld prefill parts, %lld decode parts\n", (long long)prefill, (long long)decode);
+  CHECK(prefill > 0 && decode > 0);
+  CHECK(prefill * kvx::kTileRows + decode * kvx::kDecodeMaxGroup <= kMaxParts * kvx::kTileRows);
+}
+
 }  // namespace
 
 int main(int argc, char** argv) {
@@ -191,6 +207,7 @@ int main(int argc, char** argv) {
   else if (what == "search") check_search_time();
   else if (what == "limits") check_limited_splits();
   else if (what == "fits") check_all_that_fits();
+  else if (what == "bound") check_bound_on_parts();
   else return 2;
   std::printf("passed\n");
   return 0;

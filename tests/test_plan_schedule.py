@@ -74,6 +74,6 @@ def test_plans_in_kernel_arguments_expand_to_the_uploaded_units(tmp_path):
 
 
 @needs_host_build
-@pytest.mark.parametrize("what", ["once", "search", "limits", "fits"])
+@pytest.mark.parametrize("what", ["once", "search", "limits", "fits", "bound"])
 def test_planning_of_calls(tmp_path, what):
     _host_check(tmp_path, "plan_calls", what, ["-O2"])
