@@ -181,6 +181,15 @@ void check_all_that_fits() {
     CHECK(plan_noalloc(t, h.hq, h.hkv, 128) == KVX_EHIP);
   }
   CHECK(packed >= 2);
+  // mixed: the merges of one chunked decode are too much, tiles for all fit to the last unit
+  std::vector<int32_t> P(32768, 100), E(32768, 1);
+  P[0] = 100000;
+  E[1] = 2;
+  const TestBatch t(P, E);
+  CHECK(is_mixed_batch(&t.b, 8, 8));
+  CHECK(plan_noalloc(t, 8, 8, 128) == KVX_EHIP);
+  const kvx::FixedScratch less{KVX_NOALLOC_PLAN_BYTES - 32, KVX_NOALLOC_PARTS_BYTES, no_address};
+  CHECK(plan_noalloc(t, 8, 8, 128, less) == KVX_EUNSUPPORTED);
 }
 
 // The partial results of a mixed batch, of both kinds together, stay within those of kMaxParts

@@ -6,9 +6,10 @@ import numpy as np
 import pytest
 import torch
 
-from gpu_harness import DEV, GpuRun
+from gpu_harness import DEV, GpuRun, compare, oracle_rows
 from paper_2609_32278_amd import kvx
 from paper_2609_32278_amd import workloads as wl
+from test_abi import _check_plan
 from test_gpu_extend import _run_and_compare
 
 pytestmark = pytest.mark.gpu
@@ -30,9 +31,26 @@ def test_decode_at_the_edges_of_pages_and_key_steps(dt, hq, hkv, d, split):
 
 
 # prefilling requests next to decoding ones: chunked and single-chunk decode prefixes, an
-# empty prefix (one key), a request with no suffix; enough one-token work for the mixed launch
-MIXED_P = [0, 4000, 9000, 33, 15000, 700, 2047, 2048, 5000, 12345]
-MIXED_E = [1, 1, 1, 130, 1, 40, 1, 1, 0, 1]
+# empty prefix (one key), a request with no suffix, a prefill tile that a split of 1024 keys
+# cuts into parts; enough one-token work for the mixed launch
+MIXED_P = [0, 4000, 9000, 33, 15000, 700, 2047, 2048, 5000, 12345, 6000]
+MIXED_E = [1, 1, 1, 130, 1, 40, 1, 1, 0, 1, 150]
+
+
+def _check_mixed(w, split):
+    """The batch's plan has decode units: chunks of 512 keys (2048 at most, as many as give 512
+    units) or of the forced split, whose parts are numbered after the prefill tiles'."""
+    items = _check_plan(w, split)
+    one = w.extend_lens[items["req"]] == 1
+    keys = w.num_kv_heads * int((w.prefix_lens[w.extend_lens == 1] + 1).sum())
+    chunk = split or min(2048, max(512, keys // 512)) // 64 * 64
+    starts = np.unique(items["key_begin"][items["req"] == 4])
+    assert np.array_equal(starts, np.arange(0, 15001, chunk))
+    tiles = items["part"][~one & (items["part"] >= 0)]
+    chunks = items["part"][one & (items["part"] >= 0)]
+    assert len(chunks) and chunks.min() == len(tiles)
+    if split:
+        assert 10 in items["req"][~one & (items["part"] >= 0)]
 
 
 @pytest.mark.parametrize("dt", [wl.KV_BF16, wl.KV_FP8_E4M3])
@@ -40,12 +58,37 @@ MIXED_E = [1, 1, 1, 130, 1, 40, 1, 1, 0, 1]
 @pytest.mark.parametrize("split,scaled_q", [(0, False), (1024, False), (0, True)])
 def test_batches_that_mix_prefill_and_decode(dt, hq, hkv, d, split, scaled_q):
     w = wl.make_custom(MIXED_P, MIXED_E, hq, hkv, d, kv_dtype=dt, seed=62)
-    b = kvx.Batch(w.prefix_lens, w.extend_lens, w.page_indptr, 0)
-    items = kvx.extend_attention_plan(b, hq, hkv, d, split)
-    assert (np.diff(np.unique(items["key_begin"][(items["req"] == 4)])) <= 2048).all()  # decode chunks
+    _check_mixed(w, split)
     # decode units are always exact: compare with the exact attention at the standard gate
     _run_and_compare(w, f"mixed_{dt}_{hq}_{hkv}_{d}_{split}_{int(scaled_q)}", want_lse=True, fill=NAN_FILL[dt],
                      split_keys=split, scaled_q=scaled_q)
+
+
+@pytest.mark.parametrize("dt,hq,hkv,d,split", [
+    (wl.KV_BF16, 32, 4, 128, 1024), (wl.KV_FP8_E4M3, 32, 4, 128, 1024), (wl.KV_BF16, 12, 6, 64, 1024),
+    (wl.KV_BF16, 32, 4, 128, 0),
+    (wl.KV_BF16, 32, 4, 128, 64),  # more parts than the scratch holds of either kind: lengths are doubled
+])
+def test_mixed_batches_in_the_fixed_scratch(dt, hq, hkv, d, split):
+    """The allocation-free call of a mixed batch: prefill and decode parts side by side in the
+    scratch.  The bits of extend_attention where neither is limited, else the oracle's gate."""
+    w = wl.make_custom(MIXED_P, MIXED_E, hq, hkv, d, kv_dtype=dt, seed=62)
+    _check_mixed(w, split)
+    print(f"[mixed] noalloc {dt} {hq}/{hkv}/{d} split {split}", flush=True)
+    run = GpuRun(w, fill_bits=NAN_FILL[dt], split_keys=split)
+    try:
+        run.store()
+        want, want_lse = run.attend(want_lse=True)
+        out, lse = torch.full_like(want, float("nan")), torch.full_like(want_lse, float("nan"))
+        kvx.extend_attention_noalloc(run.pool, run.batch, run.q, hq, w.sm_scale, out, lse)
+        torch.cuda.synchronize()
+        if split == 1024:
+            assert torch.equal(out.view(torch.int16), want.view(torch.int16)) and torch.equal(lse, want_lse)
+        (ref, ref_lse), gidx = oracle_rows(w, run.q, None, want_lse=True)
+        compare(out.float().cpu().numpy().astype(np.float64)[gidx], ref, f"mixed noalloc split {split}")
+        assert np.abs(lse.cpu().numpy()[gidx] - ref_lse).max() <= 2e-3 * max(1.0, float(np.abs(ref_lse).max()))
+    finally:
+        run.close()
 
 
 @pytest.mark.parametrize("dt", [wl.KV_BF16, wl.KV_FP8_E4M3])
@@ -189,17 +232,39 @@ def test_decode_reads_a_shared_prefix_from_the_caches():
         kvx.kv_pool_destroy(pool)
 
 
-@pytest.mark.parametrize("hq,hkv,prefix,extend,split", [
-    (8, 8, [700, 20], [90, 300], 0),       # eight heads side by side: one entry for eight units
-    (32, 16, [700, 20, 5], [9, 40, 33], 64),  # two heads per XCD, split parts
-    (8, 8, [8000], [200], 64),              # 126 parts a head: two launches write the plan
-    (8, 8, [15000, 9000], [40, 300], 64),   # beyond them: the plan is uploaded
-    (6, 3, [300, 77, 900], [200, 300, 64], 64),  # ungrouped units, one to three launches
-    (4, 2, [3000, 2500], [130, 100], 64),   # ungrouped, uploaded
-    (8, 8, [5000, 300, 64], [1, 1, 1], 64),  # decode: entries for eight units, merges in the arguments
-    (16, 8, [9000, 700], [1, 1], 64),       # decode: too many units, uploaded
-    (3, 3, [900, 31], [1, 1], 64),          # decode, ungrouped
+def _entries_and_tiles(items):
+    """Entries of a plan in kernel arguments, one for a unit or one for eight units that differ in
+    their KV head alone (all or none of the plan), and its tiles."""
+    entries = len(items)
+    if len(items) % 8 == 0:
+        by8 = items.reshape(-1, 8)
+        alike = all((by8[f] == by8[f][:, :1]).all() for f in ("req", "tok_begin", "key_begin"))
+        if alike and (np.diff(by8["kv_head"], axis=1) == 1).all() and (items["req"] >= 0).all():
+            entries //= 8
+    return entries, len(np.unique(items[items["req"] >= 0][["req", "tok_begin"]]))
+
+
+@pytest.mark.parametrize("hq,hkv,prefix,extend,split,inline", [
+    (8, 8, [700, 20], [90, 300], 0, True),        # eight heads side by side: one word for eight units
+    (32, 16, [700, 20, 5], [9, 40, 33], 64, True),  # two heads per XCD, split parts
+    (8, 8, [8000], [200], 64, True),              # 126 parts a head
+    (8, 8, [15000, 9000], [40, 300], 64, True),   # 539 words
+    (8, 8, [30000, 9000], [300, 300], 64, False),  # 1252 words
+    (6, 3, [300, 77, 900], [200, 300, 64], 64, True),  # a word per unit
+    (4, 2, [3000, 2500], [130, 100], 64, True),   # the same, 296 words
+    (4, 2, [12000, 9000], [130, 100], 64, False),  # 1064 words
+    (4, 2, [20] * 130, [3] * 130, 0, False),      # unsplit: 780 words of tiles and 260 of units
+    (8, 8, [20] * 130, [3] * 130, 0, True),       # 780 and 130
+    (4, 2, [20] * 170, [3] * 170, 0, False),      # tiles alone are too many
+    (8, 8, [5000, 300, 64], [1, 1, 1], 64, True),  # decode: entries for eight units, merges in the arguments
+    (16, 8, [9000, 700], [1, 1], 64, False),      # decode: too many units
+    (3, 3, [900, 31], [1, 1], 64, True),          # decode, an entry per unit
+    (3, 3, [3000], [1], 64, False),               # the same, too many
 ])
-def test_plans_in_kernel_arguments_and_uploaded(hq, hkv, prefix, extend, split):
+def test_plans_in_kernel_arguments_and_uploaded(hq, hkv, prefix, extend, split, inline):
+    """A decode plan of up to 110 entries and a prefill plan of up to 960 words (six for a tile, one
+    for an entry) travel in the kernel arguments, larger ones are uploaded."""
     w = wl.make_custom(prefix, extend, hq, hkv, 64, seed=64)
+    entries, tiles = _entries_and_tiles(_check_plan(w, split))
+    assert inline == (entries <= 110 if max(extend) == 1 else 6 * tiles + entries <= 960), (entries, tiles)
     _run_and_compare(w, f"inline_{hkv}_{prefix[0]}_{extend[0]}", want_lse=True, fill=0x7FC0, split_keys=split)

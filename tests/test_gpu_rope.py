@@ -373,18 +373,28 @@ def test_full_size_llama8b_with_fused_rope():
     compare(got, ref, f"rope-full {name}")
 
 
-@pytest.mark.parametrize("pages,hq,hkv,kv_dtype", [
-    (3, 5, 5, wl.KV_BF16),        # 4 heads per workgroup, ragged last groups of Q, K and V heads
-    (190, 40, 5, wl.KV_BF16),     # 8 heads per workgroup
-    (260, 40, 5, wl.KV_FP8_E4M3),  # 16 heads per workgroup
-    (4100, 5, 5, wl.KV_BF16),      # one workgroup takes all heads of a page
-    (4100, 4, 6, wl.KV_FP8_E4M3),
-    (4100, 0, 5, wl.KV_BF16),      # K and V alone
+HALF128 = (128, wl.RopeSpec(1e6, 128, R.HALF, True))
+
+
+@pytest.mark.parametrize("pages,hq,hkv,kv_dtype,d,spec", [
+    (3, 5, 5, wl.KV_BF16, *HALF128),        # 4 heads per workgroup, ragged last groups of Q, K and V heads
+    (190, 40, 5, wl.KV_BF16, *HALF128),     # 8 heads per workgroup
+    (260, 40, 5, wl.KV_FP8_E4M3, *HALF128),  # 16 heads per workgroup
+    (4100, 6, 6, wl.KV_FP8_E4M3, *HALF128),  # the same for many pages: 18 heads are too many for the next
+    # one workgroup takes all heads of a page (at most 16 of Q, K and V, 4096 pages and up)
+    (4100, 5, 5, wl.KV_BF16, *HALF128),
+    (4100, 6, 3, wl.KV_FP8_E4M3, *HALF128),
+    (4096, 5, 5, wl.KV_FP8_E4M3, 64, wl.RopeSpec(1e4, 64, R.INTERLEAVED, True)),  # V heads in two passes
+    (4096, 8, 2, wl.KV_FP8_E4M3, 64, wl.RopeSpec(1e4, 64, R.HALF, False)),
+    (4100, 5, 5, wl.KV_BF16, 64, wl.RopeSpec(1e4, 32, R.INTERLEAVED, False)),
+    (4100, 0, 5, wl.KV_BF16, *HALF128),     # K and V alone
+    (4100, 0, 8, wl.KV_FP8_E4M3, 128, wl.RopeSpec(1e4, 96, R.INTERLEAVED, True)),
 ])
-def test_head_groups_of_the_fused_store(pages, hq, hkv, kv_dtype):
+def test_head_groups_of_the_fused_store(pages, hq, hkv, kv_dtype, d, spec):
     """The fused store splits a page's heads over workgroups (4, 8 or 16 per group by
-    the batch's size): head counts that leave a ragged last group, at each size."""
-    CASES["head_groups"] = ([7], [16 * pages - 9], max(hq, hkv), hkv, 128, kv_dtype, wl.RopeSpec(1e6, 128, R.HALF, True))
+    the batch's size, or all of few heads): head counts that leave a ragged last group, at
+    each size."""
+    CASES["head_groups"] = ([7], [16 * pages - 9], hq or hkv, hkv, d, kv_dtype, spec)
     try:
         _check_store("head_groups", seed=5, with_q=hq > 0)
     finally:
