@@ -100,9 +100,11 @@ def code_hash(path: str) -> str:
 
 
 def attn_source_hash(config: str = "llama8b") -> str:
-    """Code hash of the attention (or decode) kernel source: committed counter
-    summaries carry it, and their traffic is used only while it matches."""
+    """Code hash of the attention (or decode) kernel source and of the planner, whose order of
+    units sets what the caches catch: committed counter summaries carry it, and their
+    traffic is used only while it matches."""
     names = ("kvx_decode.hip", "kvx_decode_unit.h") if is_decode(config) else ("kvx_attn.hip", "kvx_attn_kernels.h")
+    names += ("kvx_host.cpp",)
     paths = [os.path.join(ROOT, "paper_2609_32278_amd", "csrc", n) for n in names]
     code = "\n".join(code_only(open(p, encoding="utf-8").read()) for p in paths if os.path.exists(p))
     return hashlib.sha256(code.encode()).hexdigest()[:16]

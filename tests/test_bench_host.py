@@ -42,6 +42,10 @@ def test_traffic_is_read_only_for_the_current_kernel_source(tmp_path, monkeypatc
     assert bench.traffic_from_profiles("wide70b") == 3.5e11
     _write(src, "__global__ void k() { int x = 0; }\n")  # the kernel changed: the counters are stale
     assert bench.traffic_from_profiles("wide70b") is None
+    _write(src, "__global__ void k() {}\n")
+    assert bench.traffic_from_profiles("wide70b") == 3.5e11
+    _write(os.path.join(os.path.dirname(src), "kvx_host.cpp"), "int order() { return 1; }\n")  # the planner did
+    assert bench.traffic_from_profiles("wide70b") is None
 
 
 def test_committed_summaries_name_a_hash_in_the_current_format():
