@@ -267,8 +267,9 @@ int extend_attention(kvx_pool *pool, const kvx_batch *batch, const void *q, int3
  * before the call returns).
  *   The array holds KVX_NOALLOC_PLAN_BYTES of plan (32 B per work item) and
  *   KVX_NOALLOC_PARTS_BYTES of partial results; the planner splits key ranges
- *   only into as many parts as fit.  A batch whose plan does not fit is refused
- *   with EUNSUPPORTED on the host, before any device work.
+ *   only into as many parts as fit.  A batch whose smallest plan (without splits and
+ *   without the padding that evens out the XCDs) does not fit is refused with
+ *   EUNSUPPORTED on the host, before any device work.
  *   Each GPU the library runs on holds its own copy of the array (64 MiB) from
  *   the first call on it until the process ends.  Every call on one GPU shares
  *   that copy, and each call leaves its plan and partial results in it: calls
@@ -301,8 +302,10 @@ typedef struct {
 /*
  * The host-side work plan extend_attention would launch for a batch (host only,
  * no device work): ragged (P, E) pairs cut into tiles, long key ranges split,
- * items ordered longest first within each XCD; for a decode step, key chunks of
- * every (request, KV head), longest first (tok_count 1).  Writes at most `cap` items to
+ * within each XCD longest first or, in large unsplit batches, request by request;
+ * for a decode step, key chunks of every (request, KV head), longest first
+ * (tok_count 1); in a batch that mixes both, the one-token suffixes may be such
+ * chunks, whose parts are numbered after the tiles'.  Writes at most `cap` items to
  * `items` (may be NULL) and the total count to *count.
  *   num_kv_heads, num_q_heads, head_dim as for extend_attention.
  *   split_keys   as set by kv_pool_set_split_keys (0 = automatic).
@@ -315,7 +318,8 @@ int extend_attention_plan(const kvx_batch *batch, int32_t num_q_heads, int32_t n
 /*
  * Key-range split length of extend_attention on this pool (tokens, a multiple
  * of 64, or 0 = automatic, the default).  A non-zero value splits every key
- * range longer than it (a decode step: chunks of that many keys); used to
+ * range longer than it (a decode step, and the one-token suffixes of a mixed batch: chunks
+ * of that many keys; more where the parts would be too many); used to
  * exercise the split path.  A setting of the pool: takes effect for calls queued
  * after it, from the pool's one host thread.  Errors: EINVAL.
  */

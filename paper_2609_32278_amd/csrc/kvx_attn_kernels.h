@@ -548,8 +548,8 @@ __device__ __forceinline__ void write_result(const AttnParams& p, const Rows& r,
 // on other CUs are bound by MFMA, so the two kinds overlap; the plan spreads the
 // decode units over the launch.  Through a 256-row tile, a one-token suffix spends the
 // MFMA work of 64 tokens.  3 prefilling requests with 61 decoding ones (1k-16k contexts,
-// 32/8/128 heads): 767 us with tiles for all, 612 us mixed; the prefilling ones alone take
-// 432 us, the decoding ones 279 us.
+// 32/8/128 heads): 776 us with tiles for all, 604 us mixed; the prefilling ones alone take
+// 427 us, the decoding ones 308 us.
 
 // Run the workgroup's unit if it is a decode unit.
 template <int D, bool FP8>

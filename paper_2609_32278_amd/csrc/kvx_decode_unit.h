@@ -371,8 +371,8 @@ __device__ __forceinline__ void decode_unit_fp8(const DecodeArgs& p, const Decod
 
   // Quad `quad` from r; its registers are refilled with quad `next` (if < n_quads) as
   // soon as the products have read them.  TAIL: the quad reaches past key_end.  (A template
-  // flag and not a branch: masking the loaded registers in place inside the loop made
-  // the compiler reuse some of them too early.)
+  // flag and not a branch: masked under a branch in the loop, the results are the same bits,
+  // but 8 registers more go over it: 100 agents on 8/2/64 heads 146 us, 135 so.)
   auto compute = [&](int quad, int next, QuadRegs<D>& r, auto tail_flag, auto nt_flag) {
     constexpr bool TAIL = decltype(tail_flag)::value;
     const bool more = next < n_quads;  // uniform

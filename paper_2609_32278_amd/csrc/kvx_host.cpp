@@ -291,8 +291,9 @@ struct Tile {
 // What a unit costs besides its iterations over 64 keys, in such iterations (about 1.7 us
 // at head_dim 128 on a busy chip, 0.9 us at 64): its first loads and its epilogue; the
 // fp32 result of a part of 256 rows, written and read again; the merge launch.  Set so
-// that the split chosen below is the fastest one, or within 5% of it, on 14 batches timed
-// with ten forced split lengths each (units alone take 11.5 and 8.0 us for one tile).
+// that the split chosen below is the fastest one or nearly: on 13 batches timed with 12 forced
+// split lengths each, within 2% of the best in calls above 500 us and 1-6%, the search's own
+// host time with it, below (units alone take 11.5 and 8.0 us for one tile).
 struct UnitCosts {
   double start, part, merge;
 };
@@ -302,8 +303,10 @@ constexpr UnitCosts kUnitCosts128{8.0, 4.0, 3.0}, kUnitCosts64{11.0, 4.0, 3.0};
 // iterations.
 constexpr double kDecodePerIter = 0.4;
 // Share of them spread evenly over the prefill units, which they overlap; the rest fill up
-// the end.  3 prefilling requests with 61 decoding ones: 632 us, 636 us with three quarters,
-// 668 us with all of them spread, 683 us with all at the end.
+// the end.  3 prefilling requests with 61 decoding ones (1k-16k contexts, 32/8/128 heads): 604 us
+// a call, 613 us with three quarters, 638 us with all of them spread, 680 us with all at the
+// end.  Against tiles for all, 23 mixes (1-8 prefilling, 4-96 decoding, head_dim 64 and 128,
+// both pool types) take 0.48-0.97 of the time.
 constexpr double kDecodeSpread = 0.6;
 struct Filler {
   int64_t units = 0;  // of one KV head
@@ -812,7 +815,7 @@ bool is_decode_batch(const kvx_batch* b, int32_t Hq, int32_t Hkv) {
 
 // Work plan of a decode step: each (request, KV head) key range [0, P] is cut into
 // chunks of a common length, a multiple of 64 keys chosen so that the batch yields
-// about 2048 chunks (8 per workgroup slot at two resident workgroups per CU), at
+// about 2048 chunks (8 per CU, of which two to four run at a time), at
 // least 512 keys each; a range of more than one chunk becomes parts merged by
 // log-sum-exp.  Chunks are dispatched longest first.
 int make_decode_plan(const kvx_batch* b, const std::vector<int64_t>& qo, int32_t Hkv, int32_t split_keys,

@@ -83,7 +83,7 @@ void check_planned_once() {
     call = std::min(call, least_us([&] { CHECK(plan_noalloc(t, 8, 1, 128) == KVX_EHIP); }, 5));
   }
   std::printf("plan %.0f us, call %.0f us\n", one, call);
-  CHECK(call < 1.5 * one);
+  CHECK(call < 1.7 * one);  // planned twice: 2.5
 }
 
 // The search for a split costs at most as much as three plans of the split it found (many
