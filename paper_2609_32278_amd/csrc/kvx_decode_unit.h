@@ -71,10 +71,12 @@ struct CombineShared {
 // Lane (n, g) holds dims 16 b + 4 g + i of row n, relative to its row maximum m_run
 // (log2 units), and the part l_run of the row sum over its own keys.  A row whose sum is a
 // NaN (a NaN or an infinite score) is written as zeros, and as NaN with NANS, which is
-// what a prefill tile gives: one-token requests beside longer ones keep that.
+// what a prefill tile gives: one-token requests beside longer ones keep that.  They also
+// get a tile's `none` where no score is above -inf: 0, on an fp8 pool NaN.
 template <int D, int NW, bool NANS>
 __device__ __forceinline__ void combine_waves(const DecodeArgs& p, const DecodeUnit& u, CombineShared<D, NW> sm,
-                                              const f32x4 (&o)[D / 16], float m_run, float l_run, float vscale) {
+                                              const f32x4 (&o)[D / 16], float m_run, float l_run, float vscale,
+                                              float none) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int n = lane & 15, g = lane >> 4, G = p.group;
   const float l_row = group_sum(l_run);
@@ -101,7 +103,7 @@ __device__ __forceinline__ void combine_waves(const DecodeArgs& p, const DecodeU
         acc += e * sm.o[(w * kRows + row) * D + d];
       }
     }
-    const float val = wsum > 0.f ? acc * vscale / wsum : NANS ? acc * 0.f : 0.f;
+    const float val = wsum > 0.f ? acc * vscale / wsum : !NANS ? 0.f : wsum == 0.f ? none : acc * 0.f;
     const float lse_v = wsum > 0.f ? (M + __log2f(wsum)) * kLn2 : -INFINITY;
     if (u.part < 0) {
       const size_t orow = (size_t)u.qo_row * p.num_q_heads + u.head * G + row;
@@ -237,7 +239,8 @@ __device__ __forceinline__ void decode_unit(const DecodeArgs& p, const DecodeUni
     mx = group_max(mx) * scale;
     if (__any(mx > m_run)) {
       const float m_new = fmaxf(m_run, mx);
-      const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);  // 0 when m_run = -inf
+      // 0 when m_run = -inf; a NaN when both are, for a row without a score above -inf
+      const float alpha = NANS && m_new == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m_run - m_new);
       l_run *= alpha;
 #pragma unroll
       for (int b = 0; b < DB; b++) o[b] *= alpha;
@@ -277,7 +280,7 @@ __device__ __forceinline__ void decode_unit(const DecodeArgs& p, const DecodeUni
   else
     for (int j = wave; j < n_pairs; j += NW) compute(j, j + NW, r, std::false_type{});
 
-  combine_waves<D, NW, NANS>(p, u, sm, o, m_run, l_run, 1.0f);
+  combine_waves<D, NW, NANS>(p, u, sm, o, m_run, l_run, 1.0f, 0.f);
 }
 
 // ---------------------------------------------------------------- fp8 pool
@@ -408,7 +411,8 @@ __device__ __forceinline__ void decode_unit_fp8(const DecodeArgs& p, const Decod
     mx = group_max(mx) * scale;
     if (__any(mx > m_run)) {
       const float m_new = fmaxf(m_run, mx);
-      const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);  // 0 when m_run = -inf
+      // 0 when m_run = -inf; a NaN when both are, for a row without a score above -inf
+      const float alpha = NANS && m_new == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m_run - m_new);
       l_run *= alpha;
 #pragma unroll
       for (int b = 0; b < DB; b++) o[b] *= alpha;
@@ -459,7 +463,7 @@ __device__ __forceinline__ void decode_unit_fp8(const DecodeArgs& p, const Decod
   else
     for (; j < n_full; j += NW) compute(j, j + NW, r, std::false_type{}, std::false_type{});
   if (j < n_quads) compute(j, j + NW, r, std::true_type{}, std::false_type{});
-  combine_waves<D, NW, NANS>(p, u, sm, o, m_run, l_run, p.v_scale[u.head]);
+  combine_waves<D, NW, NANS>(p, u, sm, o, m_run, l_run, p.v_scale[u.head], __builtin_nanf(""));
 }
 
 

@@ -107,6 +107,9 @@ def test_mixed_batches_keep_nan(dt, d, split):
     want[0, 3] = True
     q[5][0, 7, 0] = float("inf")  # infinite scores of both signs
     want[5, 7] = True
+    kv[6][0][:, 2, 9] = kv[6][0][:, 2, 9].abs() + 0.125
+    q[6][0, 17, 9] = float("-inf")  # no score above -inf: zeros, on an fp8 pool NaN
+    want[6, 17] = dt == wl.KV_FP8_E4M3
     if dt == wl.KV_BF16:          # (storing codes clamps what is not finite)
         kv[1][0][1234, 1, 5] = float("nan")
         want[1, 8:16] = True
@@ -122,6 +125,7 @@ def test_mixed_batches_keep_nan(dt, d, split):
             rows = out[int(run.qo[r]):int(run.qo[r + 1])]
             got = torch.isnan(rows).cpu()
             assert torch.equal(got, want[r].expand_as(got)), (r, int(got.sum()), int(want[r].sum()))
+        assert dt == wl.KV_FP8_E4M3 or bool((out[int(run.qo[6]), 17] == 0).all())
     finally:
         run.close()
 
