@@ -1075,7 +1075,7 @@ int decode_attention(kvx_pool* pool, const kvx_batch* batch, const std::vector<i
     lists.push_back(batch->page_indptr[batch->num_reqs]);
     const size_t bytes = lists.size() * sizeof(int32_t);
     if (in_args) {
-      std::memcpy(dp.lists.in_args, lists.data(), bytes);  // no more requests than units
+      std::memcpy(dp.lists.in_args, lists.data(), bytes);  // every request has an entry of its own
     } else if (!buf.fixed || lists_at + bytes <= buf.fixed->plan_bytes) {
       blob.resize(lists_at + bytes);
       std::memcpy(blob.data() + lists_at, lists.data(), bytes);
